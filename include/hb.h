@@ -385,7 +385,8 @@ hb_status hb_layer_stage(hb_layer* layer, int32_t stage, void** dev_ptr, int64_t
 
 /* GEMM launch plans, for tests and tuning. The four GEMMs of the layer are
  * numbered HB_GEMM_QKV, HB_GEMM_O, HB_GEMM_GATE_UP, HB_GEMM_DOWN; a plan is a
- * tile-shape index in [0, hb_gemm_tile_count()) (-1: the register-staged
+ * tile-shape index in [0, hb_gemm_tile_count()) (one of them the small-batch
+ * kernel, for at most 64 tokens and no K split; -1: the register-staged
  * kernel used when K is not a multiple of 64) and a K split (1: none; > 1:
  * fp32 partials summed by a second kernel that applies the epilogue). */
 enum { HB_GEMM_QKV = 0, HB_GEMM_O = 1, HB_GEMM_GATE_UP = 2, HB_GEMM_DOWN = 3, HB_GEMM_COUNT = 4 };

@@ -81,14 +81,16 @@ struct GemmArgs {
   const uint16_t* norm_g; uint16_t* norm_out; float norm_eps;
 };
 // Tile shape, grid and K split chosen for one GEMM (cfg < 0: the
-// register-staged kernel, used when K is not a multiple of 64).
+// register-staged kernel, used when K is not a multiple of 64; for the
+// small-batch kernel tiles_n is its row tiles per workgroup).
 struct GemmPlan {
   int cfg, tiles_m, tiles_n, ksplit, kchunk;
 };
 // force_cfg >= 0 / force_ksplit > 0 restrict the choice to one tile shape /
 // one K split where that split applies (testing).
 GemmPlan plan_gemm(const GemmArgs& a, int cu_count, int force_cfg = -1, int force_ksplit = 0);
-// Number of LDS-pipelined tile shapes (valid force_cfg values are 0..count-1).
+// Number of tile shapes, the small-batch kernel among them (valid force_cfg
+// values are 0..count-1).
 int gemm_tile_count();
 // Columns of one row of split-K partial sums (gate/up: 2 N, gate then up).
 int partial_width(const GemmArgs& a);

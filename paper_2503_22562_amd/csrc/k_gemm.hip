@@ -586,6 +586,43 @@ __global__ __launch_bounds__(64 * WR * WC) void gemm_pipe_kernel(GemmArgs a, int
   }
 }
 
+// Rotation pair (columns j .. j + 3 and j + hd/2 .. of head h) of row m of the
+// QKV product: q and k rotated with the row's cos/sin, q to C, k and v to the
+// token's pool slot.
+__device__ __forceinline__ void store_qkv_pair(const GemmArgs& a, int m, int h, int j, const f32x4& lo,
+                                               const f32x4& hi) {
+  const int hd = a.hd, half = hd >> 1;
+  if (h < a.nq + a.nkv) {
+    const float* csr = a.rope_cs + (size_t)m * hd;
+    const u32x4 c4 = ld16(csr + j), s4 = ld16(csr + half + j);
+    float rl[4], rh[4];
+    for (int e = 0; e < 4; ++e) {
+      const float c = __uint_as_float(c4[e]), sn = __uint_as_float(s4[e]);
+      rl[e] = lo[e] * c - hi[e] * sn;
+      rh[e] = hi[e] * c + lo[e] * sn;
+    }
+    const u32x2 wl = {pack_bf16x2(rl[0], rl[1]), pack_bf16x2(rl[2], rl[3])};
+    const u32x2 wh = {pack_bf16x2(rh[0], rh[1]), pack_bf16x2(rh[2], rh[3])};
+    if (h < a.nq) {
+      uint16_t* dst = reinterpret_cast<uint16_t*>(a.C) + (size_t)m * a.ldc + h * hd;
+      st8(dst + j, wl);
+      st8(dst + half + j, wh);
+    } else {
+      const int slotm = a.tok_slot[m], slot = slotm & 15;
+      uint16_t* kb = a.k_pool + ((size_t)(slotm >> 4) * a.nkv + (h - a.nq)) * 16 * hd;
+      st8(kb + k_block_offset(slot, j, hd), wl);
+      st8(kb + k_block_offset(slot, half + j, hd), wh);
+    }
+    return;
+  }
+  const int slotm = a.tok_slot[m], slot = slotm & 15, g = h - a.nq - a.nkv;
+  uint16_t* vp = a.v_pool + ((size_t)(slotm >> 4) * a.nkv + g) * 16 * hd + ((slot >> 3) * hd + j) * 8 + (slot & 7);
+  for (int e = 0; e < 4; ++e) {
+    vp[8 * e] = (uint16_t)f32_to_bf16(lo[e]);
+    vp[8 * (half + e)] = (uint16_t)f32_to_bf16(hi[e]);
+  }
+}
+
 // Sum of the split-K partials in split order, then the GEMM's epilogue: for
 // the QKV GEMM the RoPE rotation of q and k and the pool scatter of k and v
 // (a work item is 4 columns of a row and their rotation partners), for
@@ -631,27 +668,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmArgs a, const fl
       const int m = b / qk_wgs, r = (b - m * qk_wgs) * 256 + threadIdx.x;
       if (r >= qk_units) return;
       const int h = r >> qs_log, j = (r & (qs - 1)) * 4;
-      const float* csr = a.rope_cs + (size_t)m * hd;
-      const f32x4 lo = sum4(m, h * hd + j), hi = sum4(m, h * hd + half + j);
-      const u32x4 c4 = ld16(csr + j), s4 = ld16(csr + half + j);
-      float rl[4], rh[4];
-      for (int e = 0; e < 4; ++e) {
-        const float c = __uint_as_float(c4[e]), sn = __uint_as_float(s4[e]);
-        rl[e] = lo[e] * c - hi[e] * sn;
-        rh[e] = hi[e] * c + lo[e] * sn;
-      }
-      const u32x2 wl = {pack_bf16x2(rl[0], rl[1]), pack_bf16x2(rl[2], rl[3])};
-      const u32x2 wh = {pack_bf16x2(rh[0], rh[1]), pack_bf16x2(rh[2], rh[3])};
-      if (h < a.nq) {
-        uint16_t* dst = reinterpret_cast<uint16_t*>(a.C) + (size_t)m * a.ldc + h * hd;
-        st8(dst + j, wl);
-        st8(dst + half + j, wh);
-      } else {
-        const int slotm = a.tok_slot[m], slot = slotm & 15;
-        uint16_t* kb = a.k_pool + ((size_t)(slotm >> 4) * a.nkv + (h - a.nq)) * 16 * hd;
-        st8(kb + k_block_offset(slot, j, hd), wl);
-        st8(kb + k_block_offset(slot, half + j, hd), wh);
-      }
+      store_qkv_pair(a, m, h, j, sum4(m, h * hd + j), sum4(m, h * hd + half + j));
       return;
     }
     const int dblocks = hd / 32;
@@ -755,6 +772,200 @@ __global__ __launch_bounds__(256) void splitk_reduce_rmsnorm_kernel(GemmArgs a, 
 
 }  // namespace gemm_detail
 
+// ---------------------------------------------------------------------------
+// Small-batch GEMM (M <= 64): HBM-bound, the weights are streamed once.
+//
+// A workgroup owns 16 RT weight rows over the whole K, so no partial sums
+// leave the chip and the epilogue (RoPE + scatter, SwiGLU, residual) needs no
+// second kernel. Its NW waves take the 64-wide K steps round-robin and sum
+// their results in LDS at the end, in wave order. Each wave fills a ring of S
+// steps of its own (its weight rows and the M activation rows, 8 rows of 128
+// bytes per 1-KB global-to-LDS load), so the K loop has no barrier. Short rings
+// (two steps from 17 rows on) let several workgroups share a CU, whose loads
+// stay in flight while one of them starts or ends. Loading MFMA operands straight into registers instead (16 rows of 64
+// bytes, neighbouring lanes in different rows) is not coalesced: gate/up of
+// the 8B layer at M = 16 took 61 us that way, against 44.5 us here.
+//
+// What bounds it: at M <= 16 the HBM stream (8B gate/up at M = 1: 40 us, 5.85
+// of the 6.1 TB/s a plain read reaches); above that the activation rows every
+// workgroup re-reads from L2, XL KB beside 2 RT KB of weights per step, hence
+// the larger row counts of stream_rows. Layer GEMMs at 8B, us, pipelined tiles
+// with K split and their reduce -> this kernel (QKV, gate/up, down):
+// M = 1 16.1 -> 13.5, 53.2 -> 40.2, 35.7 -> 24.8; M = 32 19.4 -> 15.7,
+// 56.6 -> 47.3, 41.4 -> 34.1; M = 64 22.8 -> 18.5, 69.7 -> 55.8, 42.2 -> 42.6.
+// ---------------------------------------------------------------------------
+namespace gemm_detail {
+
+// LDS bytes of one K step: 2 RT KB of weight rows and the activation rows in
+// whole 16-row MFMA tiles (rows past 8 XL are not loaded; they only reach
+// outputs that are never stored).
+__host__ __device__ constexpr int stream_stage_bytes(int xl, int rt) { return (2 * rt + 2 * ((xl + 1) / 2)) * 1024; }
+
+// Workgroups of 16 rt weight rows (gate/up: N gate and N up rows).
+inline int stream_units(const GemmArgs& a, int rt) {
+  const int rows = a.epi == GEMM_SWIGLU ? 2 * a.N : a.N;
+  return (rows + 16 * rt - 1) / (16 * rt);
+}
+
+// First weight row of 8-row group j (0 .. 2 RT - 1) of a unit. Units pair the
+// rows whose results meet in the epilogue: gate with up, and the two halves
+// of a head's rotation pairs; the first half of a unit's 16 RT rows comes
+// from the first region, the second half from the other.
+template <int EPI, int RT>
+__device__ __forceinline__ int stream_group_row(const GemmArgs& a, int unit, int j) {
+  if (EPI == GEMM_SWIGLU || EPI == GEMM_QKV_ROPE) {
+    constexpr int HR = 8 * RT;  // rows per region
+    const int second = j >= RT, l = 8 * (second ? j - RT : j);
+    if (EPI == GEMM_SWIGLU) return (second ? a.N : 0) + unit * HR + l;
+    const int half = a.hd >> 1, per = half / HR;  // units per head
+    const int h = unit / per, j0 = (unit - h * per) * HR;
+    return h * a.hd + j0 + l + (second ? half : 0);
+  }
+  return min(unit * 16 * RT + 8 * j, a.N - 8);
+}
+
+// One 64-wide K step into a wave's ring: 2 RT loads of 8 weight rows, XL of 8
+// activation rows (row groups x_rows bytes apart), XOR-swizzled as in the
+// pipelined kernel.
+template <int XL, int RT>
+__device__ __forceinline__ void stream_issue(uint8_t* p, __amdgpu_buffer_rsrc_t rx, __amdgpu_buffer_rsrc_t rw,
+                                             const uint32_t (&wo)[2 * RT], uint32_t la, uint32_t lb, uint32_t x_rows,
+                                             uint32_t kbytes) {
+  typedef __attribute__((address_space(3))) void* lds_ptr;
+#pragma unroll
+  for (int j = 0; j < 2 * RT; ++j) {
+    uint8_t* d = p + j * 1024;
+    const uint32_t so = wo[j] + kbytes;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_ptr)d, 16, lb, so, 0, 0);
+  }
+#pragma unroll
+  for (int j = 0; j < XL; ++j) {
+    uint8_t* d = p + (2 * RT + j) * 1024;
+    const uint32_t so = j * x_rows + kbytes;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_ptr)d, 16, la, so, 0, 0);
+  }
+}
+
+template <int EPI, int XL, int RT, int NW, int S>
+__global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(GemmArgs a) {
+  constexpr bool PAIR = EPI == GEMM_SWIGLU || EPI == GEMM_QKV_ROPE;
+  constexpr int MT = (XL + 1) / 2, LOADS = 2 * RT + XL;
+  constexpr int STAGE = stream_stage_bytes(XL, RT), RING = S * STAGE;
+  static_assert(RING >= RT * MT * 1024 && (S - 1) * LOADS < 64, "ring");
+  extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+  const int lane = threadIdx.x & 63, wave = wave_id(), unit = blockIdx.x;
+  const __amdgpu_buffer_rsrc_t rx = buffer_rsrc(a.A, (uint32_t)kOperandWindow);
+  const __amdgpu_buffer_rsrc_t rw = buffer_rsrc(a.B, (uint32_t)kOperandWindow);
+  uint8_t* ring = smem + wave * RING;
+  const int lrow = lane >> 3, lchunk = (lane & 7) ^ lrow;
+  const uint32_t la = 2u * (uint32_t)(lrow * a.lda + 8 * lchunk), lb = 2u * (uint32_t)(lrow * a.ldb + 8 * lchunk);
+  uint32_t wo[2 * RT];
+#pragma unroll
+  for (int j = 0; j < 2 * RT; ++j) wo[j] = 2u * (uint32_t)stream_group_row<EPI, RT>(a, unit, j) * (uint32_t)a.ldb;
+
+  const int nsteps = a.K >> 6, n = (nsteps - wave + NW - 1) / NW;  // this wave's steps: wave, wave + NW, ...
+  const uint32_t x_rows = 16u * (uint32_t)a.lda;
+  f32x4 acc[RT][MT];
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) acc[rt][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int fr = lane & 15, fg = lane >> 4;
+  const int frag = fr * 128 + ((fg ^ (fr & 7)) << 4);
+  auto step = [&](int i) {
+    const uint8_t* p = ring + (i % S) * STAGE;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      bf16x8 w[RT], x[MT];
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) w[rt] = as_bf16x8(*reinterpret_cast<const u32x4*>(p + rt * 2048 + (frag ^ (64 * h))));
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+        x[mt] = as_bf16x8(*reinterpret_cast<const u32x4*>(p + (RT + mt) * 2048 + (frag ^ (64 * h))));
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) acc[rt][mt] = mfma16x16x32(w[rt], x[mt], acc[rt][mt]);
+    }
+  };
+#pragma unroll
+  for (int i = 0; i < S; ++i)
+    if (i < n) stream_issue<XL, RT>(ring + i * STAGE, rx, rw, wo, la, lb, x_rows, 128u * (uint32_t)(wave + NW * i));
+  int i = 0;
+  for (; i + S < n; ++i) {
+    wait_vmcnt<(S - 1) * LOADS>();
+    __builtin_amdgcn_sched_barrier(0);
+    step(i);
+    wait_lgkm0();
+    __builtin_amdgcn_sched_barrier(0);
+    stream_issue<XL, RT>(ring + (i % S) * STAGE, rx, rw, wo, la, lb, x_rows, 128u * (uint32_t)(wave + NW * (i + S)));
+  }
+  wait_vmcnt<0>();
+  __builtin_amdgcn_sched_barrier(0);
+  for (; i < n; ++i) step(i);
+  wait_lgkm0();
+  __builtin_amdgcn_sched_barrier(0);
+  f32x4* own = reinterpret_cast<f32x4*>(ring);
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) own[(rt * MT + mt) * 64 + lane] = acc[rt][mt];
+  __syncthreads();
+  auto sum = [&](int t, int l) {
+    f32x4 c = reinterpret_cast<const f32x4*>(smem)[t * 64 + l];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) c += reinterpret_cast<const f32x4*>(smem + w * RING)[t * 64 + l];
+    return c;
+  };
+  // an output vector: 4 consecutive weight rows (n .. n + 3) of activation row m
+  constexpr int ITEMS = (PAIR ? 32 : 64) * RT * MT;
+  for (int it = threadIdx.x; it < ITEMS; it += 64 * NW) {
+    if constexpr (PAIR) {
+      // first-region vector and its partner in the second region: 8 rows
+      // apart in one row tile (RT 1), or RT / 2 row tiles apart
+      const int q = RT == 1 ? it & 31 : it & 63, t = RT == 1 ? it >> 5 : it >> 6;
+      const int rt = t / MT, mt = t - rt * MT;
+      const int m = 16 * mt + (q & 15), l4 = 16 * rt + ((q >> 4) << 2);  // row inside the region
+      if (m >= a.M) continue;
+      const f32x4 lo = sum(t, q), hi = RT == 1 ? sum(t, q + 32) : sum(t + RT / 2 * MT, q);
+      if (EPI == GEMM_SWIGLU) {
+        const int n0 = unit * 8 * RT + l4;
+        const u32x2 o = {pack_bf16x2(silu_f(lo[0]) * hi[0], silu_f(lo[1]) * hi[1]),
+                         pack_bf16x2(silu_f(lo[2]) * hi[2], silu_f(lo[3]) * hi[3])};
+        st8(reinterpret_cast<uint16_t*>(a.C) + (size_t)m * a.ldc + n0, o);
+      } else {
+        const int hd = a.hd, half = hd >> 1, per = half / (8 * RT);
+        const int h = unit / per, j = (unit - h * per) * 8 * RT + l4;
+        store_qkv_pair(a, m, h, j, lo, hi);
+      }
+    } else {
+      const int t = it >> 6, l = it & 63, rt = t / MT, mt = t - rt * MT;
+      const int m = 16 * mt + (l & 15), n0 = unit * 16 * RT + 16 * rt + ((l >> 4) << 2);
+      if (m >= a.M || n0 >= a.N) continue;
+      f32x4 c = sum(t, l);
+      if (EPI == GEMM_RESIDUAL && a.R) {
+        if (a.r_f32) {
+          const u32x4 rr = ld16(reinterpret_cast<const float*>(a.R) + (size_t)m * a.ldr + n0);
+          for (int j = 0; j < 4; ++j) c[j] += __uint_as_float(rr[j]);
+        } else {
+          const u32x2 rr = ld8(reinterpret_cast<const uint16_t*>(a.R) + (size_t)m * a.ldr + n0);
+          c[0] += bf16_lo(rr[0]); c[1] += bf16_hi(rr[0]);
+          c[2] += bf16_lo(rr[1]); c[3] += bf16_hi(rr[1]);
+        }
+      }
+      if (EPI == GEMM_RESIDUAL && a.c_f32) {
+        const u32x4 o = {__float_as_uint(c[0]), __float_as_uint(c[1]), __float_as_uint(c[2]), __float_as_uint(c[3])};
+        st16(reinterpret_cast<float*>(a.C) + (size_t)m * a.ldc + n0, o);
+      } else {
+        const u32x2 o = {pack_bf16x2(c[0], c[1]), pack_bf16x2(c[2], c[3])};
+        st8(reinterpret_cast<uint16_t*>(a.C) + (size_t)m * a.ldc + n0, o);
+      }
+    }
+  }
+}
+
+}  // namespace gemm_detail
+
 namespace {
 using namespace gemm_detail;
 
@@ -779,10 +990,12 @@ constexpr TileCfg kTiles[] = {
     {2, 8, 2, 2, 3, 0.911f, 0.911f, 0.690f, 0.00f},  {8, 4, 2, 4, 2, 1.525f, 1.525f, 1.353f, 8.74f},
     {6, 4, 2, 4, 2, 1.411f, 1.411f, 1.188f, 7.69f},  {4, 4, 2, 4, 3, 0.999f, 0.999f, 0.863f, 2.13f},
     {4, 8, 4, 2, 2, 1.512f, 1.512f, 1.305f, 10.75f}, {3, 8, 4, 2, 2, 1.427f, 1.427f, 1.235f, 5.37f},
-    {2, 8, 4, 2, 3, 1.000f, 1.000f, 0.857f, 4.33f},  {6, 6, 2, 4, 2, 1.636f, 1.636f, 1.499f, 12.96f},
+    {2, 8, 4, 2, 3, 1.000f, 1.000f, 0.857f, 4.33f},  {0, 0, 0, 0, 0, 0.f, 0.f, 0.f, 0.f},
     {9, 4, 2, 4, 2, 1.546f, 1.546f, 1.417f, 12.96f},
 };
 constexpr int kNumTiles = (int)(sizeof(kTiles) / sizeof(kTiles[0]));
+constexpr int kStreamTile = 13;  // the small-batch kernel's place in the tile numbering (not a pipelined tile)
+static_assert(kTiles[kStreamTile].tm == 0, "no pipelined tile");
 
 template <int TM, int TN, int WR, int WC, int ST, int EPI>
 void launch_tile(hipStream_t s, const GemmArgs& a, int tiles_m, int tiles_n, int ksplit, int kchunk, float* partial) {
@@ -810,9 +1023,61 @@ void launch_cfg(int idx, hipStream_t s, const GemmArgs& a, int tm, int tn, int k
     case 10: launch_tile<4, 8, 4, 2, 2, EPI>(s, a, tm, tn, ks, kchunk, part); break;
     case 11: launch_tile<3, 8, 4, 2, 2, EPI>(s, a, tm, tn, ks, kchunk, part); break;
     case 12: launch_tile<2, 8, 4, 2, 3, EPI>(s, a, tm, tn, ks, kchunk, part); break;
-    case 13: launch_tile<6, 6, 2, 4, 2, EPI>(s, a, tm, tn, ks, kchunk, part); break;
     default: launch_tile<9, 4, 2, 4, 2, EPI>(s, a, tm, tn, ks, kchunk, part); break;
   }
+}
+
+// 16-row weight tiles per workgroup (RT) of the small-batch kernel, 0 where the
+// pipelined tiles are the better choice.
+//
+// Above 32 rows the re-read activations outweigh the weights, and long K
+// loops amortise what a K split costs the pipelined tiles: 70B gate/up (940
+// MB) at M = 32 175 us here against 205 us, at M = 64 209 against 178 us;
+// 70B down (470 MB) 103 against 101 and 129 against 103 us; 8B gate/up
+// (235 MB) at M = 64 54 against 62-70 us. The line lies between, at 128 MiB
+// of weights (gate/up, whose partial sums are twice as wide: 256 MiB).
+//
+// RT: the least bytes through the fullest CU, ceil(units / CUs) workgroups of
+// 2 RT KB of weights and g KB of activations per step. 8B down at M = 32: RT
+// 1 (256 workgroups) 34.1 us, RT 2 (128) 41.1 us; gate/up at M = 48: RT 2
+// 54.2 us, RT 4 51.8 us. Up to 16 rows RT 1 is the best or ties (8B gate/up at
+// M = 16: 44.5 us, RT 2 45.6 us).
+constexpr int kStreamMaxM = 64;
+int stream_rows(const GemmArgs& a, int cu_count) {
+  const int g = (a.M + 7) / 8;  // 8-row activation groups
+  const int64_t rows = (int64_t)(a.epi == GEMM_SWIGLU ? 2 : 1) * a.N, cus = std::max(1, cu_count);
+  if (a.M > kStreamMaxM || (a.M > 32 && (int64_t)a.N * a.K * 2 > ((int64_t)128 << 20))) return 0;
+  int best = 1;
+  int64_t best_kb = INT64_MAX;
+  for (int rt = 1; rt <= (g <= 2 ? 1 : g <= 4 ? 2 : 4); rt *= 2) {
+    if (rt > 1 && rows % (16 * rt)) break;
+    const int64_t kb = ((rows / (16 * rt) + cus - 1) / cus) * (2 * rt + g);
+    if (kb < best_kb) best = rt, best_kb = kb;
+  }
+  return best;
+}
+
+template <int EPI, int XL, int RT>
+void launch_stream_rt(hipStream_t s, const GemmArgs& a) {
+  constexpr int NW = 4, S = XL <= 2 ? 4 : 2, lds = NW * S * stream_stage_bytes(XL, RT);
+  static_assert(lds <= 160 * 1024, "LDS");
+  static std::atomic<uint64_t> lds_raised{0};
+  raise_dynamic_lds(reinterpret_cast<const void*>(&gemm_stream_kernel<EPI, XL, RT, NW, S>), lds, lds_raised);
+  gemm_stream_kernel<EPI, XL, RT, NW, S><<<stream_units(a, RT), 64 * NW, lds, s>>>(a);
+}
+
+// Activation rows are loaded in groups of 8: up to 8, 16, 24, 32, 48 or 64.
+template <int EPI>
+void launch_stream(hipStream_t s, const GemmArgs& a, int rt) {
+  const int g = (a.M + 7) / 8;
+  if (g <= 1) launch_stream_rt<EPI, 1, 1>(s, a);
+  else if (g <= 2) launch_stream_rt<EPI, 2, 1>(s, a);
+  else if (g <= 3) rt == 1 ? launch_stream_rt<EPI, 3, 1>(s, a) : launch_stream_rt<EPI, 3, 2>(s, a);
+  else if (g <= 4) rt == 1 ? launch_stream_rt<EPI, 4, 1>(s, a) : launch_stream_rt<EPI, 4, 2>(s, a);
+  else if (g <= 6) rt == 1 ? launch_stream_rt<EPI, 6, 1>(s, a)
+                           : rt == 2 ? launch_stream_rt<EPI, 6, 2>(s, a) : launch_stream_rt<EPI, 6, 4>(s, a);
+  else rt == 1 ? launch_stream_rt<EPI, 8, 1>(s, a)
+               : rt == 2 ? launch_stream_rt<EPI, 8, 2>(s, a) : launch_stream_rt<EPI, 8, 4>(s, a);
 }
 
 // The reduce grids fit one wave of workgroups over the chip (about four per
@@ -876,7 +1141,13 @@ static int tiles_per_cu(const TileCfg& c) {
   return (c.wr * c.wc == 4 && 2 * lds <= 160 * 1024) ? 2 : 1;
 }
 
+// The small-batch kernel where it applies and nothing else is forced; else
+// the cheapest tile and split by the cost model.
 static GemmPlan search_plan(const GemmArgs& a, int cu_count, int force_cfg, int force_ksplit) {
+  if ((force_cfg < 0 || force_cfg == kStreamTile) && force_ksplit <= 1) {
+    const int rt = stream_rows(a, cu_count);
+    if (rt > 0) return GemmPlan{kStreamTile, 1, rt, 1, a.K};
+  }
   GemmPlan best{-1, 0, 0, 1, 0};
   double best_cost = 1e300;
   const int ksteps = a.K / 64;
@@ -887,7 +1158,7 @@ static GemmPlan search_plan(const GemmArgs& a, int cu_count, int force_cfg, int 
   };
   const int W = partial_width(a);
   for (int i = 0; i < kNumTiles; ++i) {
-    if (force_cfg >= 0 && i != force_cfg) continue;
+    if (i == kStreamTile || (force_cfg >= 0 && i != force_cfg)) continue;
     const TileCfg& c = kTiles[i];
     const int bm = 16 * c.tm * c.wr, bn = 16 * c.tn * c.wc;
     const int ncols = (a.epi == GEMM_SWIGLU) ? bn / 2 : bn;
@@ -925,10 +1196,20 @@ GemmPlan plan_gemm(const GemmArgs& a, int cu_count, int force_cfg, int force_ksp
   return p;
 }
 
+
 bool launch_gemm(hipStream_t s, const GemmArgs& a, const GemmPlan& p, float* partial) {
   if (a.M <= 0 || a.N <= 0) return false;
   if (p.cfg < 0) {
     launch_gemm_regstaged(s, a);
+    return false;
+  }
+  if (p.cfg == kStreamTile) {
+    switch (a.epi) {
+      case GEMM_STORE_BF16: launch_stream<GEMM_STORE_BF16>(s, a, p.tiles_n); break;
+      case GEMM_QKV_ROPE: launch_stream<GEMM_QKV_ROPE>(s, a, p.tiles_n); break;
+      case GEMM_RESIDUAL: launch_stream<GEMM_RESIDUAL>(s, a, p.tiles_n); break;
+      default: launch_stream<GEMM_SWIGLU>(s, a, p.tiles_n); break;
+    }
     return false;
   }
   switch (a.epi) {
