@@ -984,17 +984,17 @@ struct TileCfg {
 // 2374 (the first 14 shapes x splits 1, 2, 3, 4, 6, 8); the last shape's are
 // the 192 x 384 tile's scaled by their measured time ratio (0.945).
 constexpr TileCfg kTiles[] = {
-    {8, 4, 2, 2, 3, 0.978f, 0.978f, 0.920f, 0.00f},  {4, 8, 2, 2, 3, 1.046f, 1.046f, 0.850f, 4.61f},
+    {8, 4, 2, 2, 3, 0.978f, 0.978f, 0.920f, 0.00f},  {0, 0, 0, 0, 0, 0.f, 0.f, 0.f, 0.f},
     {4, 4, 2, 2, 2, 0.849f, 1.040f, 0.798f, 9.68f},  {6, 4, 2, 2, 2, 1.012f, 1.458f, 1.260f, 1.14f},
     {3, 8, 2, 2, 3, 0.961f, 0.961f, 0.779f, 0.00f},  {9, 4, 2, 2, 3, 1.073f, 1.073f, 1.039f, 0.00f},
     {2, 8, 2, 2, 3, 0.911f, 0.911f, 0.690f, 0.00f},  {8, 4, 2, 4, 2, 1.525f, 1.525f, 1.353f, 8.74f},
     {6, 4, 2, 4, 2, 1.411f, 1.411f, 1.188f, 7.69f},  {4, 4, 2, 4, 3, 0.999f, 0.999f, 0.863f, 2.13f},
     {4, 8, 4, 2, 2, 1.512f, 1.512f, 1.305f, 10.75f}, {3, 8, 4, 2, 2, 1.427f, 1.427f, 1.235f, 5.37f},
-    {2, 8, 4, 2, 3, 1.000f, 1.000f, 0.857f, 4.33f},  {0, 0, 0, 0, 0, 0.f, 0.f, 0.f, 0.f},
+    {2, 8, 4, 2, 3, 1.000f, 1.000f, 0.857f, 4.33f},  {6, 6, 2, 4, 2, 1.636f, 1.636f, 1.499f, 12.96f},
     {9, 4, 2, 4, 2, 1.546f, 1.546f, 1.417f, 12.96f},
 };
 constexpr int kNumTiles = (int)(sizeof(kTiles) / sizeof(kTiles[0]));
-constexpr int kStreamTile = 13;  // the small-batch kernel's place in the tile numbering (not a pipelined tile)
+constexpr int kStreamTile = 1;  // the small-batch kernel's place in the tile numbering (not a pipelined tile)
 static_assert(kTiles[kStreamTile].tm == 0, "no pipelined tile");
 
 template <int TM, int TN, int WR, int WC, int ST, int EPI>
@@ -1011,7 +1011,6 @@ template <int EPI>
 void launch_cfg(int idx, hipStream_t s, const GemmArgs& a, int tm, int tn, int ks, int kchunk, float* part) {
   switch (idx) {
     case 0: launch_tile<8, 4, 2, 2, 3, EPI>(s, a, tm, tn, ks, kchunk, part); break;
-    case 1: launch_tile<4, 8, 2, 2, 3, EPI>(s, a, tm, tn, ks, kchunk, part); break;
     case 2: launch_tile<4, 4, 2, 2, 2, EPI>(s, a, tm, tn, ks, kchunk, part); break;
     case 3: launch_tile<6, 4, 2, 2, 2, EPI>(s, a, tm, tn, ks, kchunk, part); break;
     case 4: launch_tile<3, 8, 2, 2, 3, EPI>(s, a, tm, tn, ks, kchunk, part); break;
@@ -1023,6 +1022,7 @@ void launch_cfg(int idx, hipStream_t s, const GemmArgs& a, int tm, int tn, int k
     case 10: launch_tile<4, 8, 4, 2, 2, EPI>(s, a, tm, tn, ks, kchunk, part); break;
     case 11: launch_tile<3, 8, 4, 2, 2, EPI>(s, a, tm, tn, ks, kchunk, part); break;
     case 12: launch_tile<2, 8, 4, 2, 3, EPI>(s, a, tm, tn, ks, kchunk, part); break;
+    case 13: launch_tile<6, 6, 2, 4, 2, EPI>(s, a, tm, tn, ks, kchunk, part); break;
     default: launch_tile<9, 4, 2, 4, 2, EPI>(s, a, tm, tn, ks, kchunk, part); break;
   }
 }
