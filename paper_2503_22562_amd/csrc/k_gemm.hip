@@ -1035,7 +1035,10 @@ void launch_cfg(int idx, hipStream_t s, const GemmArgs& a, int tm, int tn, int k
 // MB) at M = 32 175 us here against 205 us, at M = 64 209 against 178 us;
 // 70B down (470 MB) 103 against 101 and 129 against 103 us; 8B gate/up
 // (235 MB) at M = 64 54 against 62-70 us. The line lies between, at 128 MiB
-// of weights (gate/up, whose partial sums are twice as wide: 256 MiB).
+// of weights (gate/up, whose partial sums are twice as wide: 256 MiB). Above
+// 16 rows so do weights whose 256-row tiles fill the CUs one and a half times
+// without a K split: a 128256-row head at M = 24 204 us here against 191 us
+// (at M = 1 160 against 193 us, at M = 16 194 against 193 us).
 //
 // RT: the least bytes through the fullest CU, ceil(units / CUs) workgroups of
 // 2 RT KB of weights and g KB of activations per step. 8B down at M = 32: RT
@@ -1047,6 +1050,7 @@ int stream_rows(const GemmArgs& a, int cu_count) {
   const int g = (a.M + 7) / 8;  // 8-row activation groups
   const int64_t rows = (int64_t)(a.epi == GEMM_SWIGLU ? 2 : 1) * a.N, cus = std::max(1, cu_count);
   if (a.M > kStreamMaxM || (a.M > 32 && (int64_t)a.N * a.K * 2 > ((int64_t)128 << 20))) return 0;
+  if (a.M > 16 && rows >= 384 * cus) return 0;
   int best = 1;
   int64_t best_kb = INT64_MAX;
   for (int rt = 1; rt <= (g <= 2 ? 1 : g <= 4 ? 2 : 4); rt *= 2) {
