@@ -187,10 +187,17 @@ void build_plan(const Dims& d, const hb_batch_desc* desc, int cu_count, Plan* p,
     for (int i0 = 0; i0 < c; i0 += w) (is_tile(r) ? tile_keys : item_keys) += (double)d.nkv * (x + std::min(c, i0 + w));
   }
   // split lengths (multiples of 64 keys): about one round of tile workgroups
-  // (each split also writes kTileCols columns of fp32 partials), and for
-  // items about two wave slots' worth of keys per wave (4 per compute unit),
-  // at least 1024 keys, so a merged unit spans up to 4 S_i keys and most
-  // decodes need no merge kernel. When both kinds are present, tiles run
+  // (each split also writes kTileCols columns of fp32 partials). Items: a
+  // wave advances one 32-key step per memory latency (about 1.2 us), so a
+  // launch lasts at least that times its longest range, and at least its K/V
+  // bytes at the HBM rate. S_i is where the first is about 0.6 of the second,
+  // item_keys / (2.8 CUs) keys, between kMinItemKeys (shorter ranges gain less
+  // than their merge costs) and 1024; from 1024 on most decodes, up to 4 S_i
+  // keys, need no merge kernel, and S_i grows again with two wave slots' worth
+  // of keys per wave. Attention + merge, at least 1024 keys -> this rule: 8
+  // decodes of 512-8192 keys and one kv head 41 -> 13 us, 4 decodes of 8192
+  // keys and eight kv heads 42 -> 29 us, 128 decodes and one kv head 50 -> 31
+  // us, 32 decodes and eight kv heads 66 -> 63 us. When both kinds are present, tiles run
   // beside the bandwidth-bound items, and a tile is split only as far as it
   // would otherwise outlast the launch: the launch takes about the longer of
   // the items' K/V bytes at the HBM rate and the tile steps spread over the
@@ -209,8 +216,10 @@ void build_plan(const Dims& d, const hb_batch_desc* desc, int cu_count, Plan* p,
   }
   const int S_t_auto = std::max(1024, round_up((int64_t)std::min(s_t, 1.0e9) + 1, 64));
   const int S_t = opt.split_tile > 0 ? round_up(opt.split_tile, 64) : S_t_auto;
+  constexpr int kMinItemKeys = 64;
+  const int S_i_fill = std::min(1024, std::max(kMinItemKeys, round_up((int64_t)(item_keys * d.hd / 128 / (2.8 * cus)), 64)));
   const int S_i = opt.split_item > 0 ? round_up(opt.split_item, 64)
-                                     : std::max(1024, round_up((int64_t)(item_keys / (16.0 * cus)) + 1, 64));
+                                     : std::max(S_i_fill, round_up((int64_t)(item_keys / (16.0 * cus)) + 1, 64));
   p->split_tile = S_t;
   p->split_item = S_i;
 
@@ -336,7 +345,15 @@ void build_plan(const Dims& d, const hb_batch_desc* desc, int cu_count, Plan* p,
   std::vector<int32_t> units;
   units.reserve(nt + ni_units);
   const int run = opt.unit_block != 0 ? opt.unit_block : cus;
-  if (run > 0) {
+  if (run > 0 && ni_units == 0 && nt <= 2 * run) {
+    // tiles alone, at most two per CU: CU i gets the i-th longest and the
+    // i-th shortest (workgroups i and i + CUs share a CU), so that all CUs
+    // hold about the same number of steps: a fresh 2048-token chunk of the 8B
+    // layer, 512 tiles, 53.2 -> 50.8 us; longest first throughout gives the
+    // first CU 96 steps and the last 34
+    for (int a = 0; a < std::min(nt, run); ++a) units.push_back(a);
+    for (int a = nt - 1; a >= run; --a) units.push_back(a);
+  } else if (run > 0) {
     for (int a = 0, b = 0; a < nt || b < ni_units;) {
       for (int k = 0; k < run && a < nt; ++k) units.push_back(a++);
       for (int k = 0; k < run && b < ni_units; ++k) units.push_back(item_unit_codes[b++]);
