@@ -211,37 +211,53 @@ void launch_gather_rows(hipStream_t s, const uint16_t* src, int64_t n_src, const
 }
 
 // Index of the largest of V fp32 values per row (the lowest index among
-// equal maxima; NaN never wins). One workgroup per row.
-__global__ __launch_bounds__(256) void argmax_kernel(const float* __restrict__ x, int V, int32_t* __restrict__ out) {
-  __shared__ float sv[4];
-  __shared__ int si[4];
-  const float* row = x + (int64_t)blockIdx.x * V;
+// equal maxima; NaN never wins), V % 8 == 0. One workgroup per row, bound by
+// memory latency: each of 1024 threads has eight 16-byte loads in flight, so a
+// 128256-wide row takes four round trips (49 rows: 200 -> 15.6 us; 256 threads
+// of one 4-byte load each took 501).
+constexpr int kArgmaxThreads = 1024, kArgmaxLoads = 8;
+
+__device__ __forceinline__ void argmax_take(float& best, int& bi, float v, int i) {
+  if (v > best || (v == best && i < bi)) { best = v; bi = i; }
+}
+
+__global__ __launch_bounds__(kArgmaxThreads) void argmax_kernel(const float* __restrict__ x, int V,
+                                                                int32_t* __restrict__ out) {
+  __shared__ float sv[kArgmaxThreads / 64];
+  __shared__ int si[kArgmaxThreads / 64];
+  const u32x4* row = reinterpret_cast<const u32x4*>(x + (int64_t)blockIdx.x * V);
+  const int nv = V >> 2;
   float best = -INFINITY;
   int bi = 0x7FFFFFFF;
-  for (int i = threadIdx.x; i < V; i += 256) {
-    const float v = row[i];
-    if (v > best || (v == best && i < bi)) { best = v; bi = i; }
+  for (int v0 = threadIdx.x; v0 < nv; v0 += kArgmaxThreads * kArgmaxLoads) {
+    u32x4 r[kArgmaxLoads];
+#pragma unroll
+    for (int k = 0; k < kArgmaxLoads; ++k) r[k] = row[min(v0 + k * kArgmaxThreads, nv - 1)];  // repeats change nothing
+#pragma unroll
+    for (int k = 0; k < kArgmaxLoads; ++k)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        argmax_take(best, bi, __uint_as_float(r[k][j]), 4 * min(v0 + k * kArgmaxThreads, nv - 1) + j);
   }
   // wave: pairwise (value, index) maxima through lane swaps of distance 32..1
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) {
     const float ov = __shfl_xor(best, d);
     const int oi = __shfl_xor(bi, d);
-    if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
+    argmax_take(best, bi, ov, oi);
   }
   const int w = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0) { sv[w] = best; si[w] = bi; }
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int k = 1; k < 4; ++k)
-      if (sv[k] > best || (sv[k] == best && si[k] < bi)) { best = sv[k]; bi = si[k]; }
-    out[blockIdx.x] = bi == 0x7FFFFFFF ? 0 : bi;  // a row of NaNs or -inf gives 0
+    for (int k = 1; k < kArgmaxThreads / 64; ++k) argmax_take(best, bi, sv[k], si[k]);
+    out[blockIdx.x] = bi == 0x7FFFFFFF ? 0 : bi;  // a row of NaNs gives 0
   }
 }
 
 void launch_argmax(hipStream_t s, const float* x, int n_rows, int V, int32_t* out) {
   if (n_rows <= 0) return;
-  argmax_kernel<<<n_rows, 256, 0, s>>>(x, V, out);
+  argmax_kernel<<<n_rows, kArgmaxThreads, 0, s>>>(x, V, out);
 }
 
 }  // namespace hb
