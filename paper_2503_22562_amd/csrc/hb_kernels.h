@@ -98,9 +98,14 @@ int partial_width(const GemmArgs& a);
 // Returns true when the RMSNorm of the output rows was fused (see GemmArgs).
 bool launch_gemm(hipStream_t s, const GemmArgs& a, const GemmPlan& plan, float* partial);
 
-// Copy k, v [n][nkv][hd] into the pool slots of positions ctx..ctx+n-1.
+// Copy k, v [n][nkv][hd] into the pool slots of positions ctx..ctx+n-1. bt: the
+// block ids of positions 16 (ctx / 16) on, in device memory, or (inline) in host
+// memory, at most kAppendInlineBlocks of them, which travel with the launch.
+constexpr int kAppendInlineBlocks = 512;
 void launch_append_kv(hipStream_t s, const uint16_t* k, const uint16_t* v, int n_tokens, int ctx,
                       const int32_t* bt, int nkv, int hd, uint16_t* k_pool, uint16_t* v_pool);
+void launch_append_kv_inline(hipStream_t s, const uint16_t* k, const uint16_t* v, int n_tokens, int ctx,
+                             const int32_t* bt, int nkv, int hd, uint16_t* k_pool, uint16_t* v_pool);
 
 struct AttnArgs {
   const uint16_t* q;   // [T][nq*hd], rotated

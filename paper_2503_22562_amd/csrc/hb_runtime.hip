@@ -673,13 +673,21 @@ hb_status hb_append_kv(hb_layer* L, const int32_t* block_table, int32_t n_blocks
     if (block_table[i] < 0 || block_table[i] >= L->pool.num_blocks)
       return fail(HB_ERR_RANGE, "block_table[%lld] = %d outside [0, %d)", (long long)i, block_table[i],
                   L->pool.num_blocks);
+  // only the blocks from the first written one on are read
+  const int64_t b0 = context_len / 16;
+  const int32_t* ids = block_table + b0;
+  const uint16_t *ks = static_cast<const uint16_t*>(k), *vs = static_cast<const uint16_t*>(v);
+  uint16_t *kp = static_cast<uint16_t*>(L->pool.k_pool), *vp = static_cast<uint16_t*>(L->pool.v_pool);
+  if (nb - b0 <= kAppendInlineBlocks) {
+    // the ids travel with the launch: no upload, no second stream to wait for
+    launch_append_kv_inline(L->stream, ks, vs, n_tokens, context_len, ids, L->d.nkv, L->d.hd, kp, vp);
+    return check_hip("append_kv launch");
+  }
   const int32_t* bt = nullptr;
   int slot = 0;
-  hb_status st = stage_upload(L, block_table, (size_t)nb, &bt, &slot);
+  hb_status st = stage_upload(L, ids, (size_t)(nb - b0), &bt, &slot);
   if (st != HB_OK) return st;
-  launch_append_kv(L->stream, static_cast<const uint16_t*>(k), static_cast<const uint16_t*>(v), n_tokens,
-                   context_len, bt, L->d.nkv, L->d.hd, static_cast<uint16_t*>(L->pool.k_pool),
-                   static_cast<uint16_t*>(L->pool.v_pool));
+  launch_append_kv(L->stream, ks, vs, n_tokens, context_len, bt, L->d.nkv, L->d.hd, kp, vp);
   st = stage_consumed(L, slot);
   if (st != HB_OK) return st;
   return check_hip("append_kv launch");
