@@ -11,6 +11,7 @@
 // lane ends up with four consecutive output columns of one row and the
 // epilogue stores 8- or 16-byte vectors.
 #include <algorithm>
+#include <type_traits>
 
 #include "hb_device.h"
 #include "hb_kernels.h"
@@ -296,85 +297,244 @@ constexpr bool rope_in_tile(int tm, int tn, int nw, int hd) {
   return (16 * tn) % hd == 0 && (nw == 4 || tm * tn <= 32);
 }
 
-// QKV epilogue of one accumulator row (TN fragments of 4 columns, starting at
-// a head boundary nbase): q and k heads are rotated pairwise (column j with
-// j + hd/2, PAIR = hd/32 fragments apart, both in this lane) with the row's
-// cos/sin; q is stored to C, k and v to the token's pool slot.
-template <int TN, int PAIR>
-__device__ __forceinline__ void qkv_rope_row(const GemmArgs& a, const f32x4 (&acc)[TN], int m, int nbase, int cq) {
-  constexpr int HD = 32 * PAIR, HALF = HD / 2;
-  const int qk_end = (a.nq + a.nkv) * HD;
-  const int slotm = a.tok_slot[m];
-  const int blk = slotm >> 4, slot = slotm & 15;
-  const float* csr = a.rope_cs + (size_t)m * HD;
+// Rotation pair (columns j .. j + 3 and j + hd/2 .. of head h) of row m of the
+// QKV product: q and k rotated with the row's cos/sin (c4, s4: its columns j ..
+// j + 3), q to C, k to the token's pool slot.
+__device__ __forceinline__ void store_rotated_pair(const GemmArgs& a, int m, int h, int j, const f32x4& lo,
+                                                   const f32x4& hi, const u32x4& c4, const u32x4& s4) {
+  const int hd = a.hd, half = hd >> 1;
+  float rl[4], rh[4];
+  for (int e = 0; e < 4; ++e) {
+    const float c = __uint_as_float(c4[e]), sn = __uint_as_float(s4[e]);
+    rl[e] = lo[e] * c - hi[e] * sn;
+    rh[e] = hi[e] * c + lo[e] * sn;
+  }
+  const u32x2 wl = {pack_bf16x2(rl[0], rl[1]), pack_bf16x2(rl[2], rl[3])};
+  const u32x2 wh = {pack_bf16x2(rh[0], rh[1]), pack_bf16x2(rh[2], rh[3])};
+  if (h < a.nq) {
+    uint16_t* dst = reinterpret_cast<uint16_t*>(a.C) + (size_t)m * a.ldc + h * hd;
+    st8(dst + j, wl);
+    st8(dst + half + j, wh);
+  } else {
+    const int slotm = a.tok_slot[m], slot = slotm & 15;
+    uint16_t* kb = a.k_pool + ((size_t)(slotm >> 4) * a.nkv + (h - a.nq)) * 16 * hd;
+    st8(kb + k_block_offset(slot, j, hd), wl);
+    st8(kb + k_block_offset(slot, half + j, hd), wh);
+  }
+}
+
+// The same for any head: v goes to the token's pool slot as it is.
+__device__ __forceinline__ void store_qkv_pair(const GemmArgs& a, int m, int h, int j, const f32x4& lo,
+                                               const f32x4& hi) {
+  const int hd = a.hd, half = hd >> 1;
+  if (h < a.nq + a.nkv) {
+    const float* csr = a.rope_cs + (size_t)m * hd;
+    store_rotated_pair(a, m, h, j, lo, hi, ld16(csr + j), ld16(csr + half + j));
+    return;
+  }
+  const int slotm = a.tok_slot[m], slot = slotm & 15, g = h - a.nq - a.nkv;
+  uint16_t* vp = a.v_pool + ((size_t)(slotm >> 4) * a.nkv + g) * 16 * hd + ((slot >> 3) * hd + j) * 8 + (slot & 7);
+  for (int e = 0; e < 4; ++e) {
+    vp[8 * e] = (uint16_t)f32_to_bf16(lo[e]);
+    vp[8 * (half + e)] = (uint16_t)f32_to_bf16(hi[e]);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Epilogues. An accumulator fragment has neighbouring lanes in different rows
+// (lane % 16), and a memory instruction whose lanes jump between rows takes a
+// cycle per lane instead of one per 64 bytes. Each wave therefore turns its
+// 16-row blocks around in LDS (a strip of its own, no barrier: one wave's LDS
+// operations run in order) and stores them row by row, neighbouring lanes
+// along a row: 256-512 contiguous bytes per row, with the residual or cos/sin
+// loads of the next blocks in flight. 8B, us: QKV with RoPE at M = 2048 108 ->
+// 102, with a K split at M = 576 38 -> 36.5 and at M = 822 (TP2 shard) 35.5 ->
+// 32; O with its fp32 residual stream at M = 2048 74 -> 71.
+// ---------------------------------------------------------------------------
+// Floats per row of a staged block of 16 TN columns: 16 bytes of padding keep
+// the 16 rows of a column on different banks.
+template <int TN>
+constexpr int kEpiPitch = 16 * TN + 4;
+
+// Stage one block: lane (row fr, columns 16 ni + 4 fg ..).
+template <int TN>
+__device__ __forceinline__ void epi_stage(float* buf, const f32x4 (&acc)[TN], int fr, int fg) {
 #pragma unroll
-  for (int ni = 0; ni < TN; ++ni) {
-    const int n = nbase + 16 * ni + cq;
-    if (n >= a.N) continue;
-    if (n < qk_end) {
-      if ((ni % (2 * PAIR)) >= PAIR) continue;  // upper half: done with its partner
-      const f32x4 lo = acc[ni], hi = acc[ni + PAIR < TN ? ni + PAIR : TN - 1];
-      const int j = n % HD;
-      const u32x4 c4 = ld16(csr + j), s4 = ld16(csr + HALF + j);
-      float rl[4], rh[4];
+  for (int ni = 0; ni < TN; ++ni) *reinterpret_cast<f32x4*>(buf + fr * kEpiPitch<TN> + 16 * ni + 4 * fg) = acc[ni];
+}
+
+// Residual operand of one block, four columns per lane and slot j (element
+// lane + 64 j of the block's 16 x 4 TN vectors). RK: none (0), bf16 (1) or
+// fp32 (2). base is the wave's first row and column; rows past last_row and
+// columns past last_col are clamped. Addresses are a wave-uniform base and
+// 32-bit byte offsets (the 16 rows of a block span less than 4 GiB).
+template <int TN, int RK>
+struct EpiResidual {
+  std::conditional_t<RK == 1, u32x2, u32x4> v[RK == 0 ? 1 : TN];
+  __device__ __forceinline__ void load(const uint8_t* base, uint32_t ld, int row0, int last_row, int last_col, int lane) {
+    if constexpr (RK > 0) {
+      constexpr uint32_t EB = RK == 2 ? 4 : 2;
+      if (row0 > last_row) return;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float c = __uint_as_float(c4[e]), sn = __uint_as_float(s4[e]);
-        rl[e] = lo[e] * c - hi[e] * sn;
-        rh[e] = hi[e] * c + lo[e] * sn;
+      for (int j = 0; j < TN; ++j) {
+        const int e = lane + 64 * j;
+        const uint32_t off = (uint32_t)min(e / (4 * TN), last_row - row0) * (ld * EB) +
+                             (uint32_t)min(4 * (e % (4 * TN)), last_col) * EB;
+        const uint8_t* block = base + (size_t)row0 * (ld * EB);
+        if constexpr (RK == 2) v[j] = ld16(block + off);
+        else v[j] = ld8(block + off);
       }
-      const u32x2 wl = {pack_bf16x2(rl[0], rl[1]), pack_bf16x2(rl[2], rl[3])};
-      const u32x2 wh = {pack_bf16x2(rh[0], rh[1]), pack_bf16x2(rh[2], rh[3])};
-      if (n < a.nq * HD) {
-        uint16_t* dst = reinterpret_cast<uint16_t*>(a.C) + (size_t)m * a.ldc + (n - j);
-        st8(dst + j, wl);
-        st8(dst + HALF + j, wh);
-      } else {
-        const int g = (n - a.nq * HD) / HD;
-        uint16_t* kb = a.k_pool + ((size_t)blk * a.nkv + g) * 16 * HD;
-        st8(kb + k_block_offset(slot, j, HD), wl);
-        st8(kb + k_block_offset(slot, HALF + j, HD), wh);
-      }
-    } else {
-      const int g = (n - qk_end) / HD, d = n % HD;
-      uint16_t* vp = a.v_pool + ((size_t)blk * a.nkv + g) * 16 * HD + ((slot >> 3) * HD + d) * 8 + (slot & 7);
+    }
+  }
+  __device__ __forceinline__ f32x4 add(f32x4 c, int j) const {
+    if constexpr (RK == 2)
+      return c + f32x4{__uint_as_float(v[j][0]), __uint_as_float(v[j][1]), __uint_as_float(v[j][2]), __uint_as_float(v[j][3])};
+    else if constexpr (RK == 1)
+      return c + f32x4{bf16_lo(v[j][0]), bf16_hi(v[j][0]), bf16_lo(v[j][1]), bf16_hi(v[j][1])};
+    else
+      return c;
+  }
+};
+
+// Rows of fp32 (CF) or bf16, plus a residual: out has row stride ld, its rows
+// m < M and columns n < N are written. The wave's blocks start at row mw,
+// column nw.
+template <int TM, int TN, int RK, bool CF>
+__device__ __forceinline__ void epi_rows(const GemmArgs& a, float* buf, const f32x4 (&acc)[TM][TN], void* out, uint32_t ld,
+                                         int mw, int nw, int lane) {
+  if (mw >= a.M || nw >= a.N) return;
+  const int fr = lane & 15, fg = lane >> 4;
+  constexpr uint32_t EB = CF ? 4 : 2;
+  const int last_row = a.M - 1 - mw, last_col = a.N - 4 - nw;
+  const uint8_t* rbase = static_cast<const uint8_t*>(a.R) + ((size_t)mw * a.ldr + nw) * (RK == 2 ? 4 : 2);
+  uint8_t* obase = static_cast<uint8_t*>(out) + ((size_t)mw * ld + nw) * EB;
+  // residual blocks in flight ahead of the one being stored: as many as the
+  // registers hold beside the accumulators (a staged block's are free)
+  constexpr int AHEAD = TM * TN <= 32 && TN <= 4 ? 2 : 1;
+  EpiResidual<TN, RK> r[AHEAD + 1];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) vp[8 * e] = (uint16_t)f32_to_bf16(acc[ni][e]);
+  for (int p = 0; p < AHEAD; ++p)
+    if (p < TM) r[p].load(rbase, a.ldr, 16 * p, last_row, last_col, lane);
+#pragma unroll
+  for (int mi = 0; mi < TM; ++mi) {
+    if (16 * mi > last_row) return;
+    epi_stage<TN>(buf, acc[mi], fr, fg);
+    if (mi + AHEAD < TM) r[(mi + AHEAD) % (AHEAD + 1)].load(rbase, a.ldr, 16 * (mi + AHEAD), last_row, last_col, lane);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const int e = lane + 64 * j, row = e / (4 * TN), col = 4 * (e % (4 * TN));
+      const f32x4 c = r[mi % (AHEAD + 1)].add(*reinterpret_cast<const f32x4*>(buf + row * kEpiPitch<TN> + col), j);
+      if (16 * mi + row > last_row || col > last_col) continue;
+      uint8_t* o = obase + (size_t)(16 * mi) * (ld * EB) + ((uint32_t)row * (ld * EB) + (uint32_t)col * EB);
+      if (CF) st16(o, u32x4{__float_as_uint(c[0]), __float_as_uint(c[1]), __float_as_uint(c[2]), __float_as_uint(c[3])});
+      else st8(o, u32x2{pack_bf16x2(c[0], c[1]), pack_bf16x2(c[2], c[3])});
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// Split-K partial sums of gate/up: the wave's first TN / 2 fragments are gate
+// columns (at nw), the others up columns (at N + nw), in rows of 2 N.
+template <int TM, int TN>
+__device__ __forceinline__ void epi_partial_pairs(const GemmArgs& a, float* buf, const f32x4 (&acc)[TM][TN], float* out,
+                                                  int mw, int nw, int lane) {
+  const int fr = lane & 15, fg = lane >> 4;
+#pragma unroll
+  for (int mi = 0; mi < TM; ++mi) {
+    const int mb = mw + 16 * mi;
+    if (mb >= a.M) return;
+    epi_stage<TN>(buf, acc[mi], fr, fg);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const int e = lane + 64 * j, row = e / (4 * TN), col = 4 * (e % (4 * TN));
+      const f32x4 c = *reinterpret_cast<const f32x4*>(buf + row * kEpiPitch<TN> + col);
+      const bool up = col >= 8 * TN;
+      const int m = mb + row, n = nw + col - (up ? 8 * TN : 0);
+      if (m >= a.M || n >= a.N) continue;
+      st16(out + (size_t)m * 2 * a.N + (up ? a.N : 0) + n,
+           u32x4{__float_as_uint(c[0]), __float_as_uint(c[1]), __float_as_uint(c[2]), __float_as_uint(c[3])});
     }
   }
 }
 
-// One accumulator row of a plain or residual epilogue: 4 columns per
-// fragment, TN fragments 16 columns apart from column nbase. RK: residual
-// none (0), bf16 (1) or fp32 (2); CF: fp32 (else bf16) output. All residual
-// loads are issued before the first add.
-template <int TN, int RK, bool CF>
-__device__ __forceinline__ void residual_row(const GemmArgs& a, const f32x4 (&acc)[TN], int m, int nbase) {
-  f32x4 r[TN];
+// SwiGLU: silu(gate) * up of fragment pairs (ni, ni + TN / 2), stored from the
+// accumulators: half the bytes of the other epilogues and no operand to wait
+// for, so turning the blocks around in LDS gains nothing (8B gate/up at M =
+// 2048 400 us, 403 us with it).
+template <int TM, int TN>
+__device__ __forceinline__ void epi_swiglu(const GemmArgs& a, const f32x4 (&acc)[TM][TN], int mw, int nw, int lane) {
+  const int fr = lane & 15, fg = lane >> 4;
 #pragma unroll
-  for (int ni = 0; ni < TN; ++ni) {
-    const int n = min(nbase + 16 * ni, a.N - 4);
-    if (RK == 2) {
-      const u32x4 rr = ld16(reinterpret_cast<const float*>(a.R) + (size_t)m * a.ldr + n);
-      r[ni] = f32x4{__uint_as_float(rr[0]), __uint_as_float(rr[1]), __uint_as_float(rr[2]), __uint_as_float(rr[3])};
-    } else if (RK == 1) {
-      const u32x2 rr = ld8(reinterpret_cast<const uint16_t*>(a.R) + (size_t)m * a.ldr + n);
-      r[ni] = f32x4{bf16_lo(rr[0]), bf16_hi(rr[0]), bf16_lo(rr[1]), bf16_hi(rr[1])};
-    } else {
-      r[ni] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int mi = 0; mi < TM; ++mi) {
+    const int m = mw + 16 * mi + fr;
+    if (m >= a.M) continue;
+#pragma unroll
+    for (int ni = 0; ni < TN / 2; ++ni) {
+      const int n = nw + 16 * ni + 4 * fg;
+      if (n >= a.N) continue;
+      const f32x4 gt = acc[mi][ni], up = acc[mi][ni + TN / 2];
+      st8(static_cast<uint16_t*>(a.C) + (size_t)m * a.ldc + n,
+          u32x2{pack_bf16x2(silu_f(gt[0]) * up[0], silu_f(gt[1]) * up[1]),
+                pack_bf16x2(silu_f(gt[2]) * up[2], silu_f(gt[3]) * up[3])});
     }
   }
+}
+
+// QKV: the wave's 16 TN columns from nw are whole heads of HD. q and k are
+// rotated from the staged block, a lane taking 4 columns of a row and their
+// partners HD / 2 further on; v goes to its pool slots from the accumulators
+// (neighbouring lanes are neighbouring slots of a dimension).
+template <int TM, int TN, int HD>
+__device__ __forceinline__ void epi_qkv(const GemmArgs& a, float* buf, const f32x4 (&acc)[TM][TN], int mw, int nw,
+                                        int lane) {
+  constexpr int HALF = HD / 2, PAIRS = 4 * TN / 2;  // 4-column pairs per row
+  const int fr = lane & 15, fg = lane >> 4;
+  if (mw >= a.M || nw >= a.N) return;
+  const int v_col = (a.nq + a.nkv) * HD;  // first v column
+  // cos/sin of a block's pairs, loaded one block ahead
+  u32x4 cs[2][TN / 2], sn[2][TN / 2];
+  auto load_cs = [&](int mi) {
 #pragma unroll
-  for (int ni = 0; ni < TN; ++ni) {
-    const int n = nbase + 16 * ni;
-    if (n >= a.N) continue;
-    const f32x4 c = acc[ni] + r[ni];
-    if (CF) {
-      const u32x4 o = {__float_as_uint(c[0]), __float_as_uint(c[1]), __float_as_uint(c[2]), __float_as_uint(c[3])};
-      st16(reinterpret_cast<float*>(a.C) + (size_t)m * a.ldc + n, o);
-    } else {
-      const u32x2 o = {pack_bf16x2(c[0], c[1]), pack_bf16x2(c[2], c[3])};
-      st8(reinterpret_cast<uint16_t*>(a.C) + (size_t)m * a.ldc + n, o);
+    for (int j = 0; j < TN / 2; ++j) {
+      const int e = lane + 64 * j, cj = 4 * ((e % PAIRS) % (HALF / 4));
+      const float* csr = a.rope_cs + (size_t)min(mw + 16 * mi + e / PAIRS, a.M - 1) * HD + cj;
+      cs[mi & 1][j] = ld16(csr);
+      sn[mi & 1][j] = ld16(csr + HALF);
+    }
+  };
+  if (nw < v_col) load_cs(0);
+#pragma unroll
+  for (int mi = 0; mi < TM; ++mi) {
+    const int mb = mw + 16 * mi;
+    if (mb >= a.M) return;
+    if (nw < v_col) {
+      epi_stage<TN>(buf, acc[mi], fr, fg);
+      if (mi + 1 < TM) load_cs(mi + 1);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < TN / 2; ++j) {
+        const int e = lane + 64 * j, row = e / PAIRS, p = e % PAIRS;
+        const int hl = p / (HALF / 4), cj = 4 * (p % (HALF / 4));  // head of the wave's, column inside it
+        const int m = mb + row, h = nw / HD + hl;
+        if (m >= a.M || h >= a.nq + a.nkv) continue;
+        const float* b = buf + row * kEpiPitch<TN> + hl * HD + cj;
+        store_rotated_pair(a, m, h, cj, *reinterpret_cast<const f32x4*>(b), *reinterpret_cast<const f32x4*>(b + HALF),
+                           cs[mi & 1][j], sn[mi & 1][j]);
+      }
+    }
+    if (nw + 16 * TN <= v_col) continue;
+    const int m = mb + fr;
+    if (m >= a.M) continue;
+    const int slotm = a.tok_slot[m], slot = slotm & 15;
+#pragma unroll
+    for (int ni = 0; ni < TN; ++ni) {
+      const int n = nw + 16 * ni + 4 * fg;
+      if (n < v_col || n >= a.N) continue;
+      const int g = (n - v_col) / HD, d = n % HD;
+      uint16_t* vp = a.v_pool + ((size_t)(slotm >> 4) * a.nkv + g) * 16 * HD + ((slot >> 3) * HD + d) * 8 + (slot & 7);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) vp[8 * e] = (uint16_t)f32_to_bf16(acc[mi][ni][e]);
     }
   }
 }
@@ -510,116 +670,51 @@ __global__ __launch_bounds__(64 * WR * WC) void gemm_pipe_kernel(GemmArgs a, int
   }
   // the loads issued past the end land in LDS before the workgroup ends
   wait_vmcnt<0>();
-
-  // epilogue: acc[mi][ni][i] = C[m][n + i]. Fragment rows go in groups of
-  // EPB, whose loads (residual, or cos/sin and pool slots) are in flight
-  // together: one memory round trip per group, about 16 TN registers per
-  // group. The K loop's fragment registers cover that in 4-wave tiles; the
-  // 8-wave tiles (two waves per SIMD) would spill, and take one row at a time.
-  constexpr int EPB = (NW == 4 && 16 / TN > 1) ? 16 / TN : 1;
-  const int cq = fg << 2;
-#pragma unroll
-  for (int mi = 0; mi < TM; ++mi) {
-    if (mi % EPB == 0) __builtin_amdgcn_sched_barrier(0);
-    const int m = m0 + wm * WM + 16 * mi + fr;
-    if (m >= M) continue;
-    if (ksplit > 1) {
-      // fp32 partial sums, rows of partial_width(N) columns: the reduce
-      // kernel applies the epilogue (SwiGLU: gate at n, up at N + n)
-      const int W = (EPI == GEMM_SWIGLU) ? 2 * N : N;
-      float* prow = partial + ((size_t)ks * M + m) * W;
-#pragma unroll
-      for (int ni = 0; ni < TN; ++ni) {
-        int n, col;
-        if (EPI == GEMM_SWIGLU) {
-          n = nt * (BN / 2) + wn * (WN / 2) + 16 * (ni % (TN / 2)) + cq;
-          col = ni < TN / 2 ? n : N + n;
-        } else {
-          n = nt * BN + wn * WN + 16 * ni + cq;
-          col = n;
-        }
-        if (n >= N) continue;
-        const f32x4 c = acc[mi][ni];
-        st16(prow + col, u32x4{__float_as_uint(c[0]), __float_as_uint(c[1]), __float_as_uint(c[2]), __float_as_uint(c[3])});
-      }
-      continue;
-    }
-    if (EPI == GEMM_QKV_ROPE) {
-      // the planner sends tiles that cannot rotate in-tile (rope_in_tile)
-      // through a K split, so their rows are not built
-      if constexpr (rope_in_tile(TM, TN, NW, 128)) {
-        if (a.hd == 128) qkv_rope_row<TN, 4>(a, acc[mi], m, nt * BN + wn * WN, cq);
-        else qkv_rope_row<TN, 2>(a, acc[mi], m, nt * BN + wn * WN, cq);
-      } else if constexpr (rope_in_tile(TM, TN, NW, 64)) {
-        if (a.hd == 64) qkv_rope_row<TN, 2>(a, acc[mi], m, nt * BN + wn * WN, cq);
-      }
-      continue;
-    }
-    if (EPI == GEMM_SWIGLU) {
-#pragma unroll
-      for (int ni = 0; ni < TN / 2; ++ni) {
-        const int n = nt * (BN / 2) + wn * (WN / 2) + 16 * ni + cq;
-        if (n >= N) continue;
-        const f32x4 gt = acc[mi][ni], up = acc[mi][ni + TN / 2];
-        u32x2 o;
-        o[0] = pack_bf16x2(silu_f(gt[0]) * up[0], silu_f(gt[1]) * up[1]);
-        o[1] = pack_bf16x2(silu_f(gt[2]) * up[2], silu_f(gt[3]) * up[3]);
-        st8(reinterpret_cast<uint16_t*>(a.C) + (size_t)m * a.ldc + n, o);
-      }
-    } else if (EPI == GEMM_RESIDUAL) {
-      // one straight-line row per residual / output kind (the kinds are
-      // uniform over the launch)
-      const int nb = nt * BN + wn * WN + cq;
-      if (!a.R) {
-        if (a.c_f32) residual_row<TN, 0, true>(a, acc[mi], m, nb);
-        else residual_row<TN, 0, false>(a, acc[mi], m, nb);
-      } else if (a.r_f32) {
-        if (a.c_f32) residual_row<TN, 2, true>(a, acc[mi], m, nb);
-        else residual_row<TN, 2, false>(a, acc[mi], m, nb);
-      } else {
-        if (a.c_f32) residual_row<TN, 1, true>(a, acc[mi], m, nb);
-        else residual_row<TN, 1, false>(a, acc[mi], m, nb);
-      }
-    } else {
-      residual_row<TN, 0, false>(a, acc[mi], m, nt * BN + wn * WN + cq);
-    }
-  }
-}
-
-// Rotation pair (columns j .. j + 3 and j + hd/2 .. of head h) of row m of the
-// QKV product: q and k rotated with the row's cos/sin, q to C, k and v to the
-// token's pool slot.
-__device__ __forceinline__ void store_qkv_pair(const GemmArgs& a, int m, int h, int j, const f32x4& lo,
-                                               const f32x4& hi) {
-  const int hd = a.hd, half = hd >> 1;
-  if (h < a.nq + a.nkv) {
-    const float* csr = a.rope_cs + (size_t)m * hd;
-    const u32x4 c4 = ld16(csr + j), s4 = ld16(csr + half + j);
-    float rl[4], rh[4];
-    for (int e = 0; e < 4; ++e) {
-      const float c = __uint_as_float(c4[e]), sn = __uint_as_float(s4[e]);
-      rl[e] = lo[e] * c - hi[e] * sn;
-      rh[e] = hi[e] * c + lo[e] * sn;
-    }
-    const u32x2 wl = {pack_bf16x2(rl[0], rl[1]), pack_bf16x2(rl[2], rl[3])};
-    const u32x2 wh = {pack_bf16x2(rh[0], rh[1]), pack_bf16x2(rh[2], rh[3])};
-    if (h < a.nq) {
-      uint16_t* dst = reinterpret_cast<uint16_t*>(a.C) + (size_t)m * a.ldc + h * hd;
-      st8(dst + j, wl);
-      st8(dst + half + j, wh);
-    } else {
-      const int slotm = a.tok_slot[m], slot = slotm & 15;
-      uint16_t* kb = a.k_pool + ((size_t)(slotm >> 4) * a.nkv + (h - a.nq)) * 16 * hd;
-      st8(kb + k_block_offset(slot, j, hd), wl);
-      st8(kb + k_block_offset(slot, half + j, hd), wh);
-    }
+  const int mw = m0 + wm * WM;
+  if (EPI == GEMM_SWIGLU && ksplit == 1) {
+    epi_swiglu<TM, TN>(a, acc, mw, nt * (BN / 2) + wn * (WN / 2), lane);
     return;
   }
-  const int slotm = a.tok_slot[m], slot = slotm & 15, g = h - a.nq - a.nkv;
-  uint16_t* vp = a.v_pool + ((size_t)(slotm >> 4) * a.nkv + g) * 16 * hd + ((slot >> 3) * hd + j) * 8 + (slot & 7);
-  for (int e = 0; e < 4; ++e) {
-    vp[8 * e] = (uint16_t)f32_to_bf16(lo[e]);
-    vp[8 * (half + e)] = (uint16_t)f32_to_bf16(hi[e]);
+  // every wave is done with the ring before the epilogue reuses it
+  wait_lgkm0();
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+
+  static_assert(NW * 16 * kEpiPitch<TN> * 4 <= S * STAGE_BYTES, "staging strips fit the ring");
+  float* strip = reinterpret_cast<float*>(smem) + wave * 16 * kEpiPitch<TN>;
+  if (ksplit > 1) {
+    // fp32 partial sums, rows of partial_width(N) columns: the reduce kernel
+    // applies the epilogue (SwiGLU: gate at n, up at N + n)
+    float* out = partial + (size_t)ks * M * (EPI == GEMM_SWIGLU ? 2 * N : N);
+    if (EPI == GEMM_SWIGLU) epi_partial_pairs<TM, TN>(a, strip, acc, out, mw, nt * (BN / 2) + wn * (WN / 2), lane);
+    else epi_rows<TM, TN, 0, true>(a, strip, acc, out, N, mw, nt * BN + wn * WN, lane);
+    return;
+  }
+  if (EPI == GEMM_QKV_ROPE) {
+    // the planner sends tiles that cannot rotate in-tile (rope_in_tile)
+    // through a K split, so their epilogues are not built
+    const int nw = nt * BN + wn * WN;
+    if constexpr (rope_in_tile(TM, TN, NW, 128)) {
+      if (a.hd == 128) epi_qkv<TM, TN, 128>(a, strip, acc, mw, nw, lane);
+      else epi_qkv<TM, TN, 64>(a, strip, acc, mw, nw, lane);
+    } else if constexpr (rope_in_tile(TM, TN, NW, 64)) {
+      if (a.hd == 64) epi_qkv<TM, TN, 64>(a, strip, acc, mw, nw, lane);
+    }
+  } else if (EPI != GEMM_SWIGLU) {
+    const int nw = nt * BN + wn * WN;
+    const uint32_t ld = a.ldc;
+    if (EPI == GEMM_STORE_BF16) {
+      epi_rows<TM, TN, 0, false>(a, strip, acc, a.C, ld, mw, nw, lane);
+    } else if (!a.R) {
+      if (a.c_f32) epi_rows<TM, TN, 0, true>(a, strip, acc, a.C, ld, mw, nw, lane);
+      else epi_rows<TM, TN, 0, false>(a, strip, acc, a.C, ld, mw, nw, lane);
+    } else if (a.r_f32) {
+      if (a.c_f32) epi_rows<TM, TN, 2, true>(a, strip, acc, a.C, ld, mw, nw, lane);
+      else epi_rows<TM, TN, 2, false>(a, strip, acc, a.C, ld, mw, nw, lane);
+    } else {
+      if (a.c_f32) epi_rows<TM, TN, 1, true>(a, strip, acc, a.C, ld, mw, nw, lane);
+      else epi_rows<TM, TN, 1, false>(a, strip, acc, a.C, ld, mw, nw, lane);
+    }
   }
 }
 
