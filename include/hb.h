@@ -162,8 +162,9 @@ hb_status hb_run_iteration(hb_layer* layer, const hb_batch_desc* desc);
 
 /* hb_run_iteration for callers that cannot allocate device memory during the
  * call (code under HIP graph capture, tight serving loops, harnesses that
- * forbid hipMalloc): the same kernels and launch plans, with the iteration's
- * scratch -- its metadata, split-K partial sums and attention split partials
+ * forbid hipMalloc): the same kernels and launch plans (except that a GEMM's
+ * K split whose partial sums do not fit the scratch gives way to the best plan
+ * that does), with the iteration's scratch -- its metadata, split-K partial sums and attention split partials
  * -- in a fixed 64 MiB device array that the library holds on each GPU it
  * runs on for the life of the process (looked up when a layer is created),
  * and the metadata staged through pinned host memory the layer allocated at

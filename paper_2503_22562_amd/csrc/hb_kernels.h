@@ -87,8 +87,10 @@ struct GemmPlan {
   int cfg, tiles_m, tiles_n, ksplit, kchunk;
 };
 // force_cfg >= 0 / force_ksplit > 0 restrict the choice to one tile shape /
-// one K split where that split applies (testing).
-GemmPlan plan_gemm(const GemmArgs& a, int cu_count, int force_cfg = -1, int force_ksplit = 0);
+// one K split where that split applies (testing). max_partial: the most fp32
+// partial sums a split may need.
+GemmPlan plan_gemm(const GemmArgs& a, int cu_count, int force_cfg = -1, int force_ksplit = 0,
+                   double max_partial = 1e300);
 // Number of tile shapes, the small-batch kernel among them (valid force_cfg
 // values are 0..count-1).
 int gemm_tile_count();

@@ -715,14 +715,23 @@ hb_status hb_run_iteration_noalloc(hb_layer* L, const hb_batch_desc* desc) {
   layer_gemms(d, p.T, L, desc, g);
   GemmPlan pl[HB_GEMM_COUNT];
   size_t splitk_floats = 0;
-  for (int i = 0; i < HB_GEMM_COUNT; ++i) {
-    pl[i] = plan_gemm(g[i], L->cu_count, L->gemm_tile, L->gemm_ksplit);
-    if (pl[i].ksplit > 1) splitk_floats = std::max(splitk_floats, (size_t)pl[i].ksplit * g[i].M * partial_width(g[i]));
-  }
+  auto plan_all = [&](double max_partial) {
+    splitk_floats = 0;
+    for (int i = 0; i < HB_GEMM_COUNT; ++i) {
+      pl[i] = plan_gemm(g[i], L->cu_count, L->gemm_tile, L->gemm_ksplit, max_partial);
+      if (pl[i].ksplit > 1) splitk_floats = std::max(splitk_floats, (size_t)pl[i].ksplit * g[i].M * partial_width(g[i]));
+    }
+  };
+  plan_all(1e300);
   // scratch layout: metadata | split-K partials | attention partials (o, then m and l)
   auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
   const size_t meta_bytes = p.meta.size() * sizeof(int32_t);
   const size_t off_splitk = up(meta_bytes);
+  const size_t attn_bytes = up((size_t)p.n_slots * d.hd * sizeof(float)) + up((size_t)p.n_slots * 2 * sizeof(float));
+  // a K split that does not fit gives way to the best one that does
+  if (L->gemm_ksplit <= 0 && off_splitk + attn_bytes <= kScratchBytes &&
+      off_splitk + up(splitk_floats * sizeof(float)) + attn_bytes > kScratchBytes)
+    plan_all((double)((kScratchBytes - off_splitk - attn_bytes) / 256 * 64));
   const size_t off_part_o = off_splitk + up(splitk_floats * sizeof(float));
   const size_t off_part_ml = off_part_o + up((size_t)p.n_slots * d.hd * sizeof(float));
   const size_t need = off_part_ml + up((size_t)p.n_slots * 2 * sizeof(float));

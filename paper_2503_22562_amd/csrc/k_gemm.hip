@@ -11,6 +11,7 @@
 // lane ends up with four consecutive output columns of one row and the
 // epilogue stores 8- or 16-byte vectors.
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "hb_device.h"
@@ -1066,27 +1067,29 @@ using namespace gemm_detail;
 
 struct TileCfg {
   int tm, tn, wr, wc, stages;  // per-wave MFMA blocks, wave grid, LDS stages
-  // measured cost (us) of one 64-wide K stage: in a launch's first round with
-  // one workgroup per CU, in a first round with two per CU (4-wave tiles with
-  // small LDS rings only), in each later round (the weights then come from
-  // the caches, not HBM); and a fixed cost per round
-  float first_alone_us, first_pair_us, next_us, fixed_us;
+  // fitted cost (us): one 64-wide K stage of a workgroup that waits for nothing
+  // but itself, and a round's start and end
+  float stage_us, round_us;
 };
 // Accumulators and both fragment sets stay within the 256 VGPRs of a wave.
 // 8-wave workgroups put two waves on each SIMD; 4-wave ones with LDS rings
-// of at most 80 KB run two workgroups per CU. The costs were fitted to
-// MI355X timings of the layer's four GEMMs at M = 384, 576, 1056, 2048 and
-// 2374 (the first 14 shapes x splits 1, 2, 3, 4, 6, 8); the last shape's are
-// the 192 x 384 tile's scaled by their measured time ratio (0.945).
+// of at most 80 KB run two workgroups per CU. The shapes are the fourteen that
+// lose least against the best of 50 (and against the planner before them) over
+// the four GEMMs of the 8B and 70B layers and their shards at 15-21 row counts
+// from 80 to 2563, 312 cases in all. Small and middle row counts gain from
+// rings of three and four stages under 128-column tiles, where the earlier
+// shapes had two stages or 256 columns: 8B, us, before -> now: gate/up at M =
+// 112 72 -> 53, at M = 160 75 -> 58, down at M = 160 47.6 -> 41.2, O at M = 240
+// 26 -> 21; over the 312 cases 6.9 % (geometric mean).
 constexpr TileCfg kTiles[] = {
-    {8, 4, 2, 2, 3, 0.978f, 0.978f, 0.920f, 0.00f},  {0, 0, 0, 0, 0, 0.f, 0.f, 0.f, 0.f},
-    {4, 4, 2, 2, 2, 0.849f, 1.040f, 0.798f, 9.68f},  {6, 4, 2, 2, 2, 1.012f, 1.458f, 1.260f, 1.14f},
-    {3, 8, 2, 2, 3, 0.961f, 0.961f, 0.779f, 0.00f},  {9, 4, 2, 2, 3, 1.073f, 1.073f, 1.039f, 0.00f},
-    {2, 8, 2, 2, 3, 0.911f, 0.911f, 0.690f, 0.00f},  {8, 4, 2, 4, 2, 1.525f, 1.525f, 1.353f, 8.74f},
-    {6, 4, 2, 4, 2, 1.411f, 1.411f, 1.188f, 7.69f},  {4, 4, 2, 4, 3, 0.999f, 0.999f, 0.863f, 2.13f},
-    {4, 8, 4, 2, 2, 1.512f, 1.512f, 1.305f, 10.75f}, {3, 8, 4, 2, 2, 1.427f, 1.427f, 1.235f, 5.37f},
-    {2, 8, 4, 2, 3, 1.000f, 1.000f, 0.857f, 4.33f},  {6, 6, 2, 4, 2, 1.636f, 1.636f, 1.499f, 12.96f},
-    {9, 4, 2, 4, 2, 1.546f, 1.546f, 1.417f, 12.96f},
+    {4, 4, 2, 2, 4, 0.436f, 0.850f}, {0, 0, 0, 0, 0, 0.f, 0.f},
+    {2, 4, 2, 2, 3, 0.281f, 0.004f}, {5, 4, 2, 2, 3, 0.563f, 0.835f},
+    {7, 4, 2, 2, 3, 0.691f, 1.627f}, {3, 4, 2, 2, 4, 0.377f, 0.520f},
+    {4, 4, 4, 2, 3, 0.708f, 1.269f}, {8, 4, 2, 4, 2, 1.403f, 0.095f},
+    {3, 4, 4, 2, 4, 0.533f, 1.583f}, {5, 4, 2, 4, 3, 0.888f, 1.273f},
+    {4, 8, 4, 2, 2, 1.416f, 0.577f}, {3, 8, 4, 2, 2, 1.224f, 0.010f},
+    {2, 8, 4, 2, 3, 0.756f, 0.920f}, {6, 6, 2, 4, 2, 1.584f, 0.635f},
+    {9, 4, 2, 4, 2, 1.457f, 1.256f},
 };
 constexpr int kNumTiles = (int)(sizeof(kTiles) / sizeof(kTiles[0]));
 constexpr int kStreamTile = 1;  // the small-batch kernel's place in the tile numbering (not a pipelined tile)
@@ -1105,15 +1108,15 @@ void launch_tile(hipStream_t s, const GemmArgs& a, int tiles_m, int tiles_n, int
 template <int EPI>
 void launch_cfg(int idx, hipStream_t s, const GemmArgs& a, int tm, int tn, int ks, int kchunk, float* part) {
   switch (idx) {
-    case 0: launch_tile<8, 4, 2, 2, 3, EPI>(s, a, tm, tn, ks, kchunk, part); break;
-    case 2: launch_tile<4, 4, 2, 2, 2, EPI>(s, a, tm, tn, ks, kchunk, part); break;
-    case 3: launch_tile<6, 4, 2, 2, 2, EPI>(s, a, tm, tn, ks, kchunk, part); break;
-    case 4: launch_tile<3, 8, 2, 2, 3, EPI>(s, a, tm, tn, ks, kchunk, part); break;
-    case 5: launch_tile<9, 4, 2, 2, 3, EPI>(s, a, tm, tn, ks, kchunk, part); break;
-    case 6: launch_tile<2, 8, 2, 2, 3, EPI>(s, a, tm, tn, ks, kchunk, part); break;
+    case 0: launch_tile<4, 4, 2, 2, 4, EPI>(s, a, tm, tn, ks, kchunk, part); break;
+    case 2: launch_tile<2, 4, 2, 2, 3, EPI>(s, a, tm, tn, ks, kchunk, part); break;
+    case 3: launch_tile<5, 4, 2, 2, 3, EPI>(s, a, tm, tn, ks, kchunk, part); break;
+    case 4: launch_tile<7, 4, 2, 2, 3, EPI>(s, a, tm, tn, ks, kchunk, part); break;
+    case 5: launch_tile<3, 4, 2, 2, 4, EPI>(s, a, tm, tn, ks, kchunk, part); break;
+    case 6: launch_tile<4, 4, 4, 2, 3, EPI>(s, a, tm, tn, ks, kchunk, part); break;
     case 7: launch_tile<8, 4, 2, 4, 2, EPI>(s, a, tm, tn, ks, kchunk, part); break;
-    case 8: launch_tile<6, 4, 2, 4, 2, EPI>(s, a, tm, tn, ks, kchunk, part); break;
-    case 9: launch_tile<4, 4, 2, 4, 3, EPI>(s, a, tm, tn, ks, kchunk, part); break;
+    case 8: launch_tile<3, 4, 4, 2, 4, EPI>(s, a, tm, tn, ks, kchunk, part); break;
+    case 9: launch_tile<5, 4, 2, 4, 3, EPI>(s, a, tm, tn, ks, kchunk, part); break;
     case 10: launch_tile<4, 8, 4, 2, 2, EPI>(s, a, tm, tn, ks, kchunk, part); break;
     case 11: launch_tile<3, 8, 4, 2, 2, EPI>(s, a, tm, tn, ks, kchunk, part); break;
     case 12: launch_tile<2, 8, 4, 2, 3, EPI>(s, a, tm, tn, ks, kchunk, part); break;
@@ -1230,19 +1233,51 @@ int gemm_tile_count() { return kNumTiles; }
 
 int partial_width(const GemmArgs& a) { return a.epi == GEMM_SWIGLU ? 2 * a.N : a.N; }
 
-// Cost model (microseconds): workgroups run in rounds of one (two, for small
-// LDS rings) per CU; the first round costs its K stages at the tile's
-// first-round rate (for one or two workgroups per CU), every later round at
-// the later-round rate, plus a fixed cost per round; a K split adds the fp32
-// partials' round trip (fitted at 5.1 TB/s) and the reduce launch.
 static int tiles_per_cu(const TileCfg& c) {
   const int lds = c.stages * 16 * (c.tm * c.wr + c.tn * c.wc) * 128;
   return (c.wr * c.wc == 4 && 2 * lds <= 160 * 1024) ? 2 : 1;
 }
 
+// Cost model (us): workgroups run in rounds of one (two, for small LDS rings)
+// per CU. A K stage of a round takes the 4-norm (a smooth maximum) of three
+// times: the tile's own (the same with two workgroups on a CU), its
+// distinct weight rows at the HBM rate, and all rows its workgroups load at
+// the rate the caches fill LDS. A K split adds its reduce (a launch and the
+// partials' traffic), a whole K the epilogue's own traffic. Constants fitted
+// to MI355X timings of every shape and split up to 8 in those 312 cases, each
+// launch with its reduce and the gaps; the picks take 1.8 % more than the best
+// measured choice of each case.
+struct EpilogueCost {
+  float split_us, split_bytes_us, whole_bytes_us;  // per reduce; per MB of reduce traffic; per MB of fp32 output
+};
+constexpr double kHbmBytesUs = 5.589e6, kFillBytesUs = 16.197e6, kLaterRounds = 1.025, kGemmLaunchUs = 2.684;
+// QKV + RoPE, O (with the RMSNorm behind it), gate/up, down
+constexpr EpilogueCost kEpilogueCost[] = {
+    {1.32, 1 / 7.367, 0.0}, {3.548, 1 / 7.148, 1 / 2.534}, {2.474, 1 / 7.487, 0.0}, {0.0, 1 / 5.271, 1 / 16.63}};
+
+static double plan_cost(const GemmArgs& a, const TileCfg& c, int tiles_m, int tiles_n, int ks, int kst, int cus) {
+  const int bm = 16 * c.tm * c.wr, bn = 16 * c.tn * c.wc;
+  const int slots = cus * tiles_per_cu(c), nwg = tiles_m * tiles_n * ks;
+  const int rounds = (nwg + slots - 1) / slots, last = nwg - (rounds - 1) * slots;
+  auto stage = [&](int n, double later) {  // one K stage with n workgroups in flight
+    const double own = c.stage_us * later;
+    const double hbm = (double)((n + tiles_m - 1) / tiles_m) * bn * 128.0 / kHbmBytesUs * later;
+    const double fill = (double)n * (bm + bn) * 128.0 / kFillBytesUs;
+    auto p4 = [](double x) { return x * x * x * x; };
+    return std::sqrt(std::sqrt(p4(own) + p4(hbm) + p4(fill)));
+  };
+  double us = kGemmLaunchUs + rounds * c.round_us;
+  us += kst * (rounds == 1 ? stage(last, 1.0)
+                           : stage(slots, 1.0) + (rounds - 2) * stage(slots, kLaterRounds) + stage(last, kLaterRounds));
+  const EpilogueCost& e = kEpilogueCost[a.epi == GEMM_QKV_ROPE ? 0 : a.epi == GEMM_SWIGLU ? 2 : a.r_f32 ? 3 : 1];
+  const double mb = (double)a.M * partial_width(a) * 4.0e-6;
+  return us + (ks > 1 ? e.split_us + mb * (2 * ks + 1) * e.split_bytes_us : mb * e.whole_bytes_us);
+}
+
 // The small-batch kernel where it applies and nothing else is forced; else
-// the cheapest tile and split by the cost model.
-static GemmPlan search_plan(const GemmArgs& a, int cu_count, int force_cfg, int force_ksplit) {
+// the cheapest tile and split by the cost model whose partial sums are at most
+// max_partial floats.
+static GemmPlan search_plan(const GemmArgs& a, int cu_count, int force_cfg, int force_ksplit, double max_partial) {
   if ((force_cfg < 0 || force_cfg == kStreamTile) && force_ksplit <= 1) {
     const int rt = stream_rows(a, cu_count);
     if (rt > 0) return GemmPlan{kStreamTile, 1, rt, 1, a.K};
@@ -1262,19 +1297,16 @@ static GemmPlan search_plan(const GemmArgs& a, int cu_count, int force_cfg, int 
     const int bm = 16 * c.tm * c.wr, bn = 16 * c.tn * c.wc;
     const int ncols = (a.epi == GEMM_SWIGLU) ? bn / 2 : bn;
     const int tm = (a.M + bm - 1) / bm, tn = (a.N + ncols - 1) / ncols;
-    const int slots = std::max(1, cu_count) * tiles_per_cu(c);
     for (int ks = 1; ks <= kMaxKSplit; ++ks) {
       if (ks > 1 && ksteps < 4 * ks) break;
-      if (force_ksplit > 0 && ks != force_ksplit) continue;
+      // 7 only when forced: the model has it ahead of 8 where 8 is the faster
+      // (8B down, M = 112: 41.2 against 38.6 us; M = 160: 43.9 against 41.2)
+      if (force_ksplit > 0 ? ks != force_ksplit : ks == 7) continue;
       if (!fits(c, ks)) continue;
       const int kst = (ksteps + ks - 1) / ks;
       if ((ks - 1) * kst >= ksteps) continue;  // every split gets at least one stage
-      const int nwg = tm * tn * ks;
-      const int cus = std::max(1, cu_count);
-      const int rounds = (nwg + slots - 1) / slots;
-      const float first = (slots > cus && nwg > cus) ? c.first_pair_us : c.first_alone_us;
-      double cost = kst * (first + (rounds - 1) * c.next_us) + rounds * c.fixed_us;
-      if (ks > 1) cost += (double)a.M * W * 4.0 * (2 * ks + 1) / 5.12e6 + 1.6;
+      if (ks > 1 && (double)ks * a.M * W > max_partial) continue;
+      const double cost = plan_cost(a, c, tm, tn, ks, kst, std::max(1, cu_count));
       if (cost < best_cost * 0.999) {
         best_cost = cost;
         best = GemmPlan{i, tm, tn, ks, kst * 64};
@@ -1284,14 +1316,14 @@ static GemmPlan search_plan(const GemmArgs& a, int cu_count, int force_cfg, int 
   return best;
 }
 
-GemmPlan plan_gemm(const GemmArgs& a, int cu_count, int force_cfg, int force_ksplit) {
+GemmPlan plan_gemm(const GemmArgs& a, int cu_count, int force_cfg, int force_ksplit, double max_partial) {
   if (a.K % 64 != 0 || a.N % 8 != 0) return GemmPlan{-1, 0, 0, 1, 0};
   if (force_cfg >= kNumTiles) force_cfg = -1;
   // a forced shape or split that cannot run this GEMM is relaxed: first the
   // split, then the shape
-  GemmPlan p = search_plan(a, cu_count, force_cfg, force_ksplit);
-  if (p.cfg < 0) p = search_plan(a, cu_count, force_cfg, 0);
-  if (p.cfg < 0) p = search_plan(a, cu_count, -1, 0);
+  GemmPlan p = search_plan(a, cu_count, force_cfg, force_ksplit, max_partial);
+  if (p.cfg < 0) p = search_plan(a, cu_count, force_cfg, 0, max_partial);
+  if (p.cfg < 0) p = search_plan(a, cu_count, -1, 0, max_partial);
   return p;
 }
 
