@@ -191,8 +191,8 @@ void build_plan(const Dims& d, const hb_batch_desc* desc, int cu_count, Plan* p,
   // wave advances one 32-key step per memory latency (about 1.2 us), so a
   // launch lasts at least that times its longest range, and at least its K/V
   // bytes at the HBM rate. S_i is where the first is about 0.6 of the second,
-  // item_keys / (2.8 CUs) keys, between kMinItemKeys (shorter ranges gain less
-  // than their merge costs) and 1024; from 1024 on most decodes, up to 4 S_i
+  // item_keys / (2.8 CUs) keys, between opt.min_item (64: shorter ranges gain
+  // less than their merge costs) and 1024; from 1024 on most decodes, up to 4 S_i
   // keys, need no merge kernel, and S_i grows again with two wave slots' worth
   // of keys per wave. Attention + merge, at least 1024 keys -> this rule: 8
   // decodes of 512-8192 keys and one kv head 41 -> 13 us, 4 decodes of 8192
@@ -216,8 +216,7 @@ void build_plan(const Dims& d, const hb_batch_desc* desc, int cu_count, Plan* p,
   }
   const int S_t_auto = std::max(1024, round_up((int64_t)std::min(s_t, 1.0e9) + 1, 64));
   const int S_t = opt.split_tile > 0 ? round_up(opt.split_tile, 64) : S_t_auto;
-  constexpr int kMinItemKeys = 64;
-  const int S_i_fill = std::min(1024, std::max(kMinItemKeys, round_up((int64_t)(item_keys * d.hd / 128 / (2.8 * cus)), 64)));
+  const int S_i_fill = std::min(1024, std::max(opt.min_item, round_up((int64_t)(item_keys * d.hd / 128 / (2.8 * cus)), 64)));
   const int S_i = opt.split_item > 0 ? round_up(opt.split_item, 64)
                                      : std::max(S_i_fill, round_up((int64_t)(item_keys / (16.0 * cus)) + 1, 64));
   p->split_tile = S_t;

@@ -96,6 +96,7 @@ hb_status check_batch(const Dims& d, int num_blocks, const hb_batch_desc* desc, 
 // for tuning and tests.
 struct PlanOptions {
   int split_tile = 0, split_item = 0;
+  int min_item = 64;   // least item split the planner chooses by itself
   int unit_block = 0;  // runs of tiles / item groups in the unit order (0: one per CU; < 0: fine interleave)
 };
 

@@ -708,33 +708,42 @@ hb_status hb_run_iteration_noalloc(hb_layer* L, const hb_batch_desc* desc) {
   if (st != HB_OK) return st;
   if (desc->n_requests == 0) return HB_OK;
   const Dims& d = L->d;
-  build_plan(d, desc, L->cu_count, &L->plan, L->plan_opt);
   const Plan& p = L->plan;
   Prepared pp;
-  GemmArgs g[HB_GEMM_COUNT];
-  layer_gemms(d, p.T, L, desc, g);
   GemmPlan pl[HB_GEMM_COUNT];
-  size_t splitk_floats = 0;
-  auto plan_all = [&](double max_partial) {
-    splitk_floats = 0;
-    for (int i = 0; i < HB_GEMM_COUNT; ++i) {
-      pl[i] = plan_gemm(g[i], L->cu_count, L->gemm_tile, L->gemm_ksplit, max_partial);
-      if (pl[i].ksplit > 1) splitk_floats = std::max(splitk_floats, (size_t)pl[i].ksplit * g[i].M * partial_width(g[i]));
-    }
-  };
-  plan_all(1e300);
+  GemmArgs g[HB_GEMM_COUNT];
   // scratch layout: metadata | split-K partials | attention partials (o, then m and l)
   auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
-  const size_t meta_bytes = p.meta.size() * sizeof(int32_t);
-  const size_t off_splitk = up(meta_bytes);
-  const size_t attn_bytes = up((size_t)p.n_slots * d.hd * sizeof(float)) + up((size_t)p.n_slots * 2 * sizeof(float));
-  // a K split that does not fit gives way to the best one that does
-  if (L->gemm_ksplit <= 0 && off_splitk + attn_bytes <= kScratchBytes &&
-      off_splitk + up(splitk_floats * sizeof(float)) + attn_bytes > kScratchBytes)
-    plan_all((double)((kScratchBytes - off_splitk - attn_bytes) / 256 * 64));
-  const size_t off_part_o = off_splitk + up(splitk_floats * sizeof(float));
-  const size_t off_part_ml = off_part_o + up((size_t)p.n_slots * d.hd * sizeof(float));
-  const size_t need = off_part_ml + up((size_t)p.n_slots * 2 * sizeof(float));
+  size_t meta_bytes = 0, off_splitk = 0, off_part_o = 0, off_part_ml = 0, need = 0;
+  auto plan_all = [&](const PlanOptions& opt) {
+    build_plan(d, desc, L->cu_count, &L->plan, opt);
+    layer_gemms(d, p.T, L, desc, g);
+    meta_bytes = p.meta.size() * sizeof(int32_t);
+    off_splitk = up(meta_bytes);
+    const size_t part_o = up((size_t)p.n_slots * d.hd * sizeof(float));
+    const size_t fixed = off_splitk + part_o + up((size_t)p.n_slots * 2 * sizeof(float));
+    // a K split whose partials do not fit beside the rest gives way to the best one that does
+    double max_partial = 1e300;
+    for (int pass = 0; pass < 2; ++pass) {
+      size_t floats = 0;
+      for (int i = 0; i < HB_GEMM_COUNT; ++i) {
+        pl[i] = plan_gemm(g[i], L->cu_count, L->gemm_tile, L->gemm_ksplit, max_partial);
+        if (pl[i].ksplit > 1) floats = std::max(floats, (size_t)pl[i].ksplit * g[i].M * partial_width(g[i]));
+      }
+      off_part_o = off_splitk + up(floats * sizeof(float));
+      off_part_ml = off_part_o + part_o;
+      need = fixed + up(floats * sizeof(float));
+      if (need <= kScratchBytes || fixed > kScratchBytes || L->gemm_ksplit > 0) break;
+      max_partial = (double)((kScratchBytes - fixed) / 256 * 64);
+    }
+    return need <= kScratchBytes && p.meta.size() <= kNoAllocMetaInts;
+  };
+  PlanOptions opt = L->plan_opt;
+  if (!plan_all(opt)) {
+    // items cut no finer than 1024 keys need the least metadata and partials
+    opt.min_item = 1024;
+    plan_all(opt);
+  }
   if (need > kScratchBytes || p.meta.size() > kNoAllocMetaInts)
     return fail(HB_ERR_UNSUPPORTED,
                 "batch needs %zu B of scratch (%zu B of metadata), the allocation-free entry point has %zu B "

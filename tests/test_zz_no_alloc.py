@@ -85,3 +85,58 @@ def test_noalloc_rejects_batches_beyond_its_scratch(hb, monkeypatch):
     torch.cuda.synchronize()
     assert np.array_equal(bf16_bits(dl.k_pool), k0) and np.array_equal(bf16_bits(dl.v_pool), v0)
     assert torch.all(y == 7.0)
+
+
+def test_noalloc_plans_a_smaller_k_split_when_partials_do_not_fit(hb):
+    # gate/up at 512 rows: the planner's K split 4 leaves 4 x 512 x 8192 fp32
+    # partials, exactly the 64 MiB of scratch, and the metadata needs some of it
+    import torch
+    from hb_workloads import LayerShape, make_batch, make_weights
+    from paper_2503_22562_amd import hb as H
+    from paper_2503_22562_amd.harness import DeviceLayer, to_device_bf16
+    shape = LayerShape("wide-partials", 8192, 4, 2, 64, 4096, weight_seed=45)
+    w = make_weights(shape)
+    b = make_batch(shape, [(511, 0), (1, 0)], seed=65, num_blocks=64)
+    dl = DeviceLayer(shape, w, b.num_blocks, b.n_tokens, 2)
+    reqs = [(q.chunk_len, q.context_len, q.block_table) for q in b.requests]
+    x = to_device_bf16(b.x_in())
+    y = dl.run(reqs, x)
+    torch.cuda.synchronize()
+    free_plans = H.hb_layer_gemm_plans(dl.layer)
+    y_na = torch.full_like(y, float("nan"))
+    H.hb_run_iteration_noalloc(dl.layer, reqs, x, y_na)
+    torch.cuda.synchronize()
+    plans = H.hb_layer_gemm_plans(dl.layer)
+    widths = [shape.qkv_dim, shape.hidden, 2 * shape.ffn_dim, shape.hidden]
+    partials = lambda ps: max(ks * b.n_tokens * n * 4 for (_, ks), n in zip(ps, widths) if ks > 1)
+    assert partials(free_plans) == 64 << 20 > partials(plans), (free_plans, plans)
+    ref = oracle_for_batch(b, oracle.weights_to_f64(w))
+    assert_parity(y.cpu().numpy(), ref)
+    assert_parity(y_na.cpu().numpy(), ref)
+
+
+def test_noalloc_cuts_items_coarser_when_metadata_does_not_fit(hb):
+    # 94 chunks of 1000 tokens and 16 decodes: about 264 700 int32 of metadata
+    # with the decodes cut finely, 258 400 with 1024-key items; the staging
+    # holds 262 144
+    import torch
+    from hb_workloads import LayerShape, make_batch, make_weights
+    from paper_2503_22562_amd import hb as H
+    from paper_2503_22562_amd.harness import DeviceLayer, to_device_bf16
+    shape = LayerShape("long-metadata", 256, 8, 4, 64, 128, weight_seed=46)
+    w = make_weights(shape)
+    b = make_batch(shape, [(1000, 0)] * 94 + [(1, 5000)] * 16, seed=66, num_blocks=94 * 63 + 16 * 313)
+    dl = DeviceLayer(shape, w, b.num_blocks, b.n_tokens, len(b.requests))
+    for i, q in enumerate(b.requests):
+        if q.context_len:
+            k, v = b.prior_kv(i)
+            dl.append_kv(q.block_table, 0, k, v)
+    reqs = [(q.chunk_len, q.context_len, q.block_table) for q in b.requests]
+    x = to_device_bf16(b.x_in())
+    y = dl.run(reqs, x)
+    y_na = torch.full_like(y, float("nan"))
+    H.hb_run_iteration_noalloc(dl.layer, reqs, x, y_na)
+    torch.cuda.synchronize()
+    got, want = y_na.cpu().numpy(), y.cpu().numpy()
+    assert np.array_equal(got[:94000], want[:94000])  # chunks: the same work units
+    assert_parity(got[94000:], want[94000:])          # decodes: the same keys over other splits
