@@ -878,9 +878,10 @@ __global__ __launch_bounds__(256) void splitk_reduce_rmsnorm_kernel(GemmArgs a, 
 // steps of its own (its weight rows and the M activation rows, 8 rows of 128
 // bytes per 1-KB global-to-LDS load), so the K loop has no barrier. Short rings
 // (two steps from 17 rows on) let several workgroups share a CU, whose loads
-// stay in flight while one of them starts or ends. Loading MFMA operands straight into registers instead (16 rows of 64
-// bytes, neighbouring lanes in different rows) is not coalesced: gate/up of
-// the 8B layer at M = 16 took 61 us that way, against 44.5 us here.
+// stay in flight while one of them starts or ends. Loading MFMA operands
+// straight into registers instead (16 rows of 64 bytes, neighbouring lanes in
+// different rows) is not coalesced: gate/up of the 8B layer at M = 16 took
+// 61 us that way, against 44.5 us here.
 //
 // What bounds it: at M <= 16 the HBM stream (8B gate/up at M = 1: 40 us, 5.85
 // of the 6.1 TB/s a plain read reaches); above that the activation rows every
