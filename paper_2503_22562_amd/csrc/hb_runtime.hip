@@ -37,12 +37,21 @@ namespace {
 constexpr int kStages = 4;
 // Pinned host staging of the allocation-free entry point's metadata (int32).
 constexpr size_t kNoAllocMetaInts = (size_t)1 << 18;
+// Metadata of at most this many int32 is copied by a kernel on the layer's own
+// stream: it costs a launch and one PCIe round trip, where the copy stream's
+// path costs two event waits and a DMA start ahead of the first kernel (one 8B
+// decode 121.8 -> 108.1 us, 32 decodes 190.6 -> 179.7, 777-token chunk + 45
+// decodes on a TP2 shard 299.0 -> 291.6). With 256 decodes (about 45 K int32)
+// the transfer has eaten the gain (596 us both ways); beyond 64 K the copy
+// stream hides it behind the previous iteration.
+constexpr size_t kInStreamMetaInts = (size_t)1 << 16;
 constexpr int kMaxDevices = 64;
 constexpr double kPeakHbm = 8.0e12;      // MI355X HBM3E, bytes/s
 constexpr double kPeakBf16 = 2.5e15;     // MI355X dense bf16 MFMA, flop/s
 
 // One slot of the metadata ring: pinned host staging and its device copy.
-// The upload runs on the layer's copy stream, so it overlaps the previous
+// A small upload is a kernel on the layer's stream (kInStreamMetaInts). A
+// larger one runs on the layer's copy stream, so it overlaps the previous
 // iteration's kernels; the layer's stream waits for it (copied), and the
 // next upload into the slot waits for the kernels that read it (consumed).
 struct Stage {
@@ -51,7 +60,8 @@ struct Stage {
   int32_t* dev = nullptr;
   size_t dev_cap = 0;
   hipEvent_t copied = nullptr, consumed = nullptr;
-  bool pending = false;     // copied / consumed recorded, not yet waited on by the host
+  hipEvent_t host_free = nullptr;  // the one of the two after which `host` may be refilled
+  bool pending = false;     // host_free recorded, not yet waited on by the host
 };
 
 struct TimedLaunch {
@@ -169,6 +179,21 @@ hb_status ensure_parts(hb_layer* L, int n) {
   return HB_OK;
 }
 
+hb_status check_hip(const char* what) {
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return fail(HB_ERR_HIP, "%s: %s", what, hipGetErrorString(e));
+  return HB_OK;
+}
+
+// A stream under graph capture keeps the copy stream's path, which capture
+// refuses: a graph must not read a ring slot that later calls refill.
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  const bool known = hipStreamIsCapturing(s, &st) == hipSuccess;
+  if (!known) (void)hipGetLastError();
+  return !known || st != hipStreamCaptureStatusNone;
+}
+
 // Upload `n` int32 through the next slot of the staging ring; *dev receives
 // the slot's device copy, valid for the work enqueued on the layer's stream
 // until stage_consumed(L, slot) is called after that work.
@@ -177,7 +202,7 @@ hb_status stage_upload(hb_layer* L, const int32_t* src, size_t n, const int32_t*
   Stage& s = L->stage[k];
   L->stage_next = (L->stage_next + 1) % kStages;
   if (s.pending) {
-    HB_HIP(hipEventSynchronize(s.copied));  // the host buffer is free again
+    HB_HIP(hipEventSynchronize(s.host_free));
     s.pending = false;
   }
   if (n > s.cap) {
@@ -200,13 +225,20 @@ hb_status stage_upload(hb_layer* L, const int32_t* src, size_t n, const int32_t*
     s.dev_cap = cap;
   }
   std::memcpy(s.host, src, n * sizeof(int32_t));
+  *dev = s.dev;
+  *slot = k;
+  if (n <= kInStreamMetaInts && !capturing(L->stream)) {
+    launch_copy_words(L->stream, s.host, s.dev, n);
+    s.host_free = s.consumed;  // recorded by stage_consumed
+    s.pending = true;
+    return check_hip("metadata upload");
+  }
   HB_HIP(hipStreamWaitEvent(L->copy_stream, s.consumed, 0));
   HB_HIP(hipMemcpyAsync(s.dev, s.host, n * sizeof(int32_t), hipMemcpyHostToDevice, L->copy_stream));
   HB_HIP(hipEventRecord(s.copied, L->copy_stream));
   HB_HIP(hipStreamWaitEvent(L->stream, s.copied, 0));
+  s.host_free = s.copied;
   s.pending = true;
-  *dev = s.dev;
-  *slot = k;
   return HB_OK;
 }
 
@@ -285,12 +317,6 @@ void free_layer(hb_layer* L) {
   }
   for (hipEvent_t e : L->ev_free) (void)hipEventDestroy(e);
   delete L;
-}
-
-hb_status check_hip(const char* what) {
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return fail(HB_ERR_HIP, "%s: %s", what, hipGetErrorString(e));
-  return HB_OK;
 }
 
 // A planned batch made ready to launch: GEMM shapes and plans, workspaces
@@ -755,7 +781,9 @@ hb_status hb_run_iteration_noalloc(hb_layer* L, const hb_batch_desc* desc) {
     L->na_pending = false;
   }
   std::memcpy(L->na_host, p.meta.data(), meta_bytes);
-  HB_HIP(hipMemcpyAsync(L->scratch, L->na_host, meta_bytes, hipMemcpyHostToDevice, L->stream));
+  launch_copy_words(L->stream, L->na_host, reinterpret_cast<int32_t*>(L->scratch), p.meta.size());
+  st = check_hip("metadata upload");
+  if (st != HB_OK) return st;
   HB_HIP(hipEventRecord(L->na_copied, L->stream));
   L->na_pending = true;
   pp.gq = g[HB_GEMM_QKV]; pp.go = g[HB_GEMM_O]; pp.gu = g[HB_GEMM_GATE_UP]; pp.gd = g[HB_GEMM_DOWN];

@@ -103,6 +103,23 @@ void launch_rmsnorm(hipStream_t s, const void* x, bool x_f32, const uint16_t* g,
 }
 
 // ---------------------------------------------------------------------------
+// Metadata upload: a 16-byte load per thread from pinned host memory, all in
+// flight together, so a batch's metadata takes one round trip over PCIe. In
+// place of hipMemcpyAsync on the same stream: 8 decodes of a 70B TP8 shard
+// (allocation-free entry) 91.5 -> 78.5 us per call.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void copy_words_kernel(const u32x4* __restrict__ src, u32x4* __restrict__ dst, int n) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n) dst[i] = src[i];
+}
+
+void launch_copy_words(hipStream_t s, const int32_t* host, int32_t* dev, size_t n) {
+  const int nv = (int)((n + 3) / 4);
+  if (nv == 0) return;
+  copy_words_kernel<<<(nv + 255) / 256, 256, 0, s>>>(reinterpret_cast<const u32x4*>(host), reinterpret_cast<u32x4*>(dev), nv);
+}
+
+// ---------------------------------------------------------------------------
 // KV append: a copy into the pool's layouts.
 // ---------------------------------------------------------------------------
 namespace {
