@@ -103,6 +103,9 @@ bool launch_gemm(hipStream_t s, const GemmArgs& a, const GemmPlan& plan, float* 
 // Copy n int32 of pinned host memory to the device. Both are 16-byte aligned and
 // hold n rounded up to 4.
 void launch_copy_words(hipStream_t s, const int32_t* host, int32_t* dev, size_t n);
+// The same, with the words as arguments of the launches (host may be any memory
+// and is free again on return).
+void launch_store_words(hipStream_t s, const int32_t* host, int32_t* dev, size_t n);
 
 // Copy k, v [n][nkv][hd] into the pool slots of positions ctx..ctx+n-1. bt: the
 // block ids of positions 16 (ctx / 16) on, in device memory, or (inline) in host

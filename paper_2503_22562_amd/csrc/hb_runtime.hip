@@ -775,17 +775,23 @@ hb_status hb_run_iteration_noalloc(hb_layer* L, const hb_batch_desc* desc) {
                 "batch needs %zu B of scratch (%zu B of metadata), the allocation-free entry point has %zu B "
                 "(%zu B of metadata staging); use hb_run_iteration",
                 need, meta_bytes, kScratchBytes, kNoAllocMetaInts * sizeof(int32_t));
-  // the pinned staging is reused once the previous copy out of it is done
-  if (L->na_pending) {
-    HB_HIP(hipEventSynchronize(L->na_copied));
-    L->na_pending = false;
+  if (capturing(L->stream)) {
+    // a replay must not read the staging, which any other call refills, and an
+    // event recorded under capture is not one the next call could wait for
+    launch_store_words(L->stream, p.meta.data(), reinterpret_cast<int32_t*>(L->scratch), p.meta.size());
+  } else {
+    // the pinned staging is reused once the previous copy out of it is done
+    if (L->na_pending) {
+      HB_HIP(hipEventSynchronize(L->na_copied));
+      L->na_pending = false;
+    }
+    std::memcpy(L->na_host, p.meta.data(), meta_bytes);
+    launch_copy_words(L->stream, L->na_host, reinterpret_cast<int32_t*>(L->scratch), p.meta.size());
+    st = check_hip("metadata upload");
+    if (st != HB_OK) return st;
+    HB_HIP(hipEventRecord(L->na_copied, L->stream));
+    L->na_pending = true;
   }
-  std::memcpy(L->na_host, p.meta.data(), meta_bytes);
-  launch_copy_words(L->stream, L->na_host, reinterpret_cast<int32_t*>(L->scratch), p.meta.size());
-  st = check_hip("metadata upload");
-  if (st != HB_OK) return st;
-  HB_HIP(hipEventRecord(L->na_copied, L->stream));
-  L->na_pending = true;
   pp.gq = g[HB_GEMM_QKV]; pp.go = g[HB_GEMM_O]; pp.gu = g[HB_GEMM_GATE_UP]; pp.gd = g[HB_GEMM_DOWN];
   pp.pq = pl[HB_GEMM_QKV]; pp.po = pl[HB_GEMM_O]; pp.pu = pl[HB_GEMM_GATE_UP]; pp.pd = pl[HB_GEMM_DOWN];
   pp.plan = &p;

@@ -1,5 +1,7 @@
 // Bandwidth-bound kernels of the layer: RMSNorm (with the RoPE inputs of the
 // QKV epilogue), the KV append copy, and the profiling fills.
+#include <algorithm>
+
 #include "hb_device.h"
 #include "hb_kernels.h"
 
@@ -117,6 +119,30 @@ void launch_copy_words(hipStream_t s, const int32_t* host, int32_t* dev, size_t 
   const int nv = (int)((n + 3) / 4);
   if (nv == 0) return;
   copy_words_kernel<<<(nv + 255) / 256, 256, 0, s>>>(reinterpret_cast<const u32x4*>(host), reinterpret_cast<u32x4*>(dev), nv);
+}
+
+// The same for a stream under graph capture: the words travel in the kernels'
+// arguments, kWordsPerLaunch at a time, so that a replay at any later time
+// writes the words of the captured call whatever the staging holds by then.
+namespace {
+constexpr int kWordsPerLaunch = 960;  // of the 4 KB a launch's arguments may take
+struct InlineWords {
+  int32_t w[kWordsPerLaunch];
+};
+
+__global__ __launch_bounds__(256) void store_words_kernel(InlineWords src, int32_t* __restrict__ dst, int n) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n) dst[i] = src.w[i];
+}
+}  // namespace
+
+void launch_store_words(hipStream_t s, const int32_t* host, int32_t* dev, size_t n) {
+  for (size_t i = 0; i < n; i += kWordsPerLaunch) {
+    InlineWords w{};
+    const int m = (int)std::min<size_t>(kWordsPerLaunch, n - i);
+    std::copy(host + i, host + i + m, w.w);
+    store_words_kernel<<<(m + 255) / 256, 256, 0, s>>>(w, dev + i, m);
+  }
 }
 
 // ---------------------------------------------------------------------------
