@@ -122,7 +122,8 @@ void hb_destroy_layer(hb_layer* layer);
  * Only those slots change; every other byte of the pool is left untouched.
  * Errors: HB_ERR_INVALID (null pointer, n_tokens < 0, context_len < 0,
  * n_blocks < ceil((context_len + n_tokens) / 16)), HB_ERR_RANGE (a used block
- * id outside [0, num_blocks)). n_tokens == 0 is a no-op. */
+ * id outside [0, num_blocks)), HB_ERR_HIP (among others: the layer's stream is
+ * under graph capture). n_tokens == 0 is a no-op. */
 hb_status hb_append_kv(hb_layer* layer, const int32_t* block_table, int32_t n_blocks,
                        int32_t context_len, int32_t n_tokens, const void* k, const void* v);
 
@@ -155,8 +156,9 @@ typedef struct {
 
 /* Run the decoder layer over the batch: write the new tokens' keys and values
  * into the cache, then compute x_out. Enqueues on the layer's stream.
- * Errors: as hb_validate_batch, plus HB_ERR_HIP / HB_ERR_OOM. n_requests == 0
- * is a no-op. Two requests may read the same block (shared prefix) but must
+ * Errors: as hb_validate_batch, plus HB_ERR_HIP (among others: the layer's
+ * stream is under graph capture; only hb_run_iteration_noalloc can be captured)
+ * / HB_ERR_OOM. n_requests == 0 is a no-op. Two requests may read the same block (shared prefix) but must
  * not write the same slot. */
 hb_status hb_run_iteration(hb_layer* layer, const hb_batch_desc* desc);
 

@@ -122,6 +122,7 @@ hb_status hb_run_model(hb_model* m, const hb_model_batch* b) {
   // validate through the first layer's check (all layers share shape and pool size)
   hb_batch_desc desc{b->n_requests, b->requests, m->x[0], m->x[1], HB_OUT_BF16};
   hb_status st = hb_validate_batch(&c, m->num_blocks, &desc);
+  if (st == HB_OK) st = refuse_capture(m->stream);
   if (st != HB_OK) return st;
   int T = 0;
   for (int r = 0; r < R; ++r) T += b->requests[r].chunk_len;

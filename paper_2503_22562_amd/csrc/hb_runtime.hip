@@ -185,13 +185,13 @@ hb_status check_hip(const char* what) {
   return HB_OK;
 }
 
-// A stream under graph capture keeps the copy stream's path, which capture
-// refuses: a graph must not read a ring slot that later calls refill.
+// Whether the stream is under graph capture (false where HIP cannot tell: what
+// is then enqueued reports HIP's own error).
 bool capturing(hipStream_t s) {
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  const bool known = hipStreamIsCapturing(s, &st) == hipSuccess;
-  if (!known) (void)hipGetLastError();
-  return !known || st != hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return false;
 }
 
 // Upload `n` int32 through the next slot of the staging ring; *dev receives
@@ -227,7 +227,7 @@ hb_status stage_upload(hb_layer* L, const int32_t* src, size_t n, const int32_t*
   std::memcpy(s.host, src, n * sizeof(int32_t));
   *dev = s.dev;
   *slot = k;
-  if (n <= kInStreamMetaInts && !capturing(L->stream)) {
+  if (n <= kInStreamMetaInts) {
     launch_copy_words(L->stream, s.host, s.dev, n);
     s.host_free = s.consumed;  // recorded by stage_consumed
     s.pending = true;
@@ -573,6 +573,12 @@ struct SplitMix {
 
 namespace hb {
 
+hb_status refuse_capture(hipStream_t s) {
+  if (!capturing(s)) return HB_OK;
+  return fail(HB_ERR_HIP, "the stream is under graph capture: a graph must not read a metadata slot that later calls "
+                          "refill (hb_run_iteration_noalloc can be captured)");
+}
+
 // Every layer is checked and its buffers sized before anything is enqueued,
 // so a failure leaves every pool untouched. The metadata goes through the
 // first layer's ring; its slot is released after the last layer's kernels.
@@ -704,6 +710,8 @@ hb_status hb_append_kv(hb_layer* L, const int32_t* block_table, int32_t n_blocks
   const int32_t* ids = block_table + b0;
   const uint16_t *ks = static_cast<const uint16_t*>(k), *vs = static_cast<const uint16_t*>(v);
   uint16_t *kp = static_cast<uint16_t*>(L->pool.k_pool), *vp = static_cast<uint16_t*>(L->pool.v_pool);
+  hb_status st = refuse_capture(L->stream);
+  if (st != HB_OK) return st;
   if (nb - b0 <= kAppendInlineBlocks) {
     // the ids travel with the launch: no upload, no second stream to wait for
     launch_append_kv_inline(L->stream, ks, vs, n_tokens, context_len, ids, L->d.nkv, L->d.hd, kp, vp);
@@ -711,7 +719,7 @@ hb_status hb_append_kv(hb_layer* L, const int32_t* block_table, int32_t n_blocks
   }
   const int32_t* bt = nullptr;
   int slot = 0;
-  hb_status st = stage_upload(L, ids, (size_t)(nb - b0), &bt, &slot);
+  st = stage_upload(L, ids, (size_t)(nb - b0), &bt, &slot);
   if (st != HB_OK) return st;
   launch_append_kv(L->stream, ks, vs, n_tokens, context_len, bt, L->d.nkv, L->d.hd, kp, vp);
   st = stage_consumed(L, slot);
@@ -724,6 +732,8 @@ hb_status hb_run_iteration(hb_layer* L, const hb_batch_desc* desc) {
   hb_status st = check_batch(L->d, L->pool.num_blocks, desc, &L->marks);
   if (st != HB_OK) return st;
   if (desc->n_requests == 0) return HB_OK;
+  st = refuse_capture(L->stream);
+  if (st != HB_OK) return st;
   build_plan(L->d, desc, L->cu_count, &L->plan, L->plan_opt);
   return enqueue_layer(L, desc);
 }

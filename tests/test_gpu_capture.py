@@ -1,6 +1,8 @@
-"""hb_run_iteration_noalloc under HIP graph capture: a replay computes the
-captured batch, whatever the layer ran in between (its pinned metadata staging
-is refilled by every eager call), and eager calls after a capture work."""
+"""HIP graph capture. hb_run_iteration_noalloc: a replay computes the captured
+batch, whatever the layer ran in between (its pinned metadata staging is
+refilled by every eager call), and eager calls after a capture work. The other
+enqueuing calls are refused without harm to the capture, the pool or later
+calls."""
 import numpy as np
 import pytest
 
@@ -75,3 +77,60 @@ def test_replay_runs_the_captured_batch(hb):
             assert torch.equal(y, want), i
             assert torch.equal(got, want_others[i % 3]) and torch.equal(after, want_others[(i + 1) % 3]), i
             assert all(torch.equal(p, q) for p, q in zip((dl.k_pool, dl.v_pool), pools)), i
+
+
+def test_other_calls_are_refused_under_capture(hb):
+    import torch
+    from hb_workloads import TINY, make_batch, make_model_weights
+    from paper_2503_22562_amd import hb as H
+    from paper_2503_22562_amd.harness import DeviceModel
+    rng = np.random.default_rng(93)
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        dl, gen = _layer(torch)
+        a = _batch(rng, np.arange(NB), [(30, 100), (1, 400)])
+        x = torch.randn(31, COVER.hidden, device="cuda", generator=gen).to(torch.bfloat16)
+        k = torch.randn(9000, COVER.n_kv_heads, COVER.head_dim, device="cuda", generator=gen).to(torch.bfloat16)
+        short, long = np.arange(8, dtype=np.int32), np.arange(600, dtype=np.int32)
+        b = make_batch(TINY, [(5, 0), (1, 0)], seed=94, num_blocks=16)
+        reqs = [(r.chunk_len, r.context_len, r.block_table) for r in b.requests]
+        dm = DeviceModel(TINY, make_model_weights(TINY, 2, 200), b.num_blocks, b.n_tokens, len(reqs))
+        ids = torch.from_numpy(b.token_ids(200).astype(np.int32)).cuda()
+        nxt = torch.empty(2, dtype=torch.int32, device="cuda")
+        logits = torch.empty((2, 200), dtype=torch.float32, device="cuda")
+        H.hb_run_model(dm.model, reqs, ids, nxt, logits)
+        want_logits = logits.clone()
+        y = dl.run(a, x)
+        want = y.clone()
+        count = torch.zeros(1, device="cuda")
+        side.synchronize()
+        pools = [p.clone() for p in (dl.k_pool, dl.v_pool)]
+        side.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    calls = [lambda: H.hb_run_iteration(dl.layer, a, x, y), lambda: H.hb_append_kv(dl.layer, short, 0, k[:100], k[:100]),
+             lambda: H.hb_append_kv(dl.layer, long, 5, k, k), lambda: H.hb_run_model(dm.model, reqs, ids, nxt, logits)]
+    status = []
+    with torch.cuda.graph(graph, stream=side):
+        count.add_(1)
+        for c in calls:
+            try:
+                c()
+                status.append(0)
+            except H.HBError as e:
+                status.append(e.status)
+    assert status == [H.HB_ERR_HIP] * 4
+    with torch.cuda.stream(side):
+        graph.replay()
+        graph.replay()
+        side.synchronize()
+        assert count.item() == 2  # the capture went on
+        assert all(torch.equal(p, q) for p, q in zip((dl.k_pool, dl.v_pool), pools))
+        for _ in range(6):  # more calls than the ring has slots
+            y.fill_(float("nan"))
+            H.hb_run_iteration(dl.layer, a, x, y)
+            logits.fill_(float("nan"))
+            H.hb_run_model(dm.model, reqs, ids, nxt, logits)
+            side.synchronize()
+            assert torch.equal(y, want) and torch.equal(logits, want_logits)
+        H.hb_append_kv(dl.layer, long, 5, k, k)
+        side.synchronize()
