@@ -102,6 +102,14 @@ __device__ __forceinline__ float wave_sum(float v) {
   return rows_sum(v);
 }
 
+// Between LDS accesses by which lanes of one wave exchange data. The hardware
+// runs a wave's LDS operations in order, so nothing is waited for; the fence
+// keeps the compiler, which sees one lane's addresses, from reordering them.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // Index of the calling wave in its workgroup, as a wave-uniform value (so
 // loads addressed by it become scalar loads).
 __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }

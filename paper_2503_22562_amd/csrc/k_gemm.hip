@@ -345,8 +345,8 @@ __device__ __forceinline__ void store_qkv_pair(const GemmArgs& a, int m, int h, 
 // Epilogues. An accumulator fragment has neighbouring lanes in different rows
 // (lane % 16), and a memory instruction whose lanes jump between rows takes a
 // cycle per lane instead of one per 64 bytes. Each wave therefore turns its
-// 16-row blocks around in LDS (a strip of its own, no barrier: one wave's LDS
-// operations run in order) and stores them row by row, neighbouring lanes
+// 16-row blocks around in LDS (a strip of its own, no barrier:
+// wave_lds_order) and stores them row by row, neighbouring lanes
 // along a row: 256-512 contiguous bytes per row, with the residual or cos/sin
 // loads of the next blocks in flight. 8B, us: QKV with RoPE at M = 2048 108 ->
 // 102, with a K split at M = 576 38 -> 36.5 and at M = 822 (TP2 shard) 35.5 ->
@@ -357,11 +357,14 @@ __device__ __forceinline__ void store_qkv_pair(const GemmArgs& a, int m, int h, 
 template <int TN>
 constexpr int kEpiPitch = 16 * TN + 4;
 
-// Stage one block: lane (row fr, columns 16 ni + 4 fg ..).
+// Stage one block: lane (row fr, columns 16 ni + 4 fg ..), after the other
+// lanes' reads of the block before it and before their reads of this one.
 template <int TN>
 __device__ __forceinline__ void epi_stage(float* buf, const f32x4 (&acc)[TN], int fr, int fg) {
+  wave_lds_order();
 #pragma unroll
   for (int ni = 0; ni < TN; ++ni) *reinterpret_cast<f32x4*>(buf + fr * kEpiPitch<TN> + 16 * ni + 4 * fg) = acc[ni];
+  wave_lds_order();
 }
 
 // Residual operand of one block, four columns per lane and slot j (element
