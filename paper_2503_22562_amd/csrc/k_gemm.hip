@@ -1247,17 +1247,33 @@ static int tiles_per_cu(const TileCfg& c) {
 // times: the tile's own (the same with two workgroups on a CU), its
 // distinct weight rows at the HBM rate, and all rows its workgroups load at
 // the rate the caches fill LDS. A K split adds its reduce (a launch and the
-// partials' traffic), a whole K the epilogue's own traffic. Constants fitted
-// to MI355X timings of every shape and split up to 8 in those 312 cases, each
-// launch with its reduce and the gaps; the picks take 1.5 % more than the best
-// measured choice of each case.
+// partials' traffic), a whole K the epilogue's own traffic and, behind the O
+// projection, the RMSNorm launch that the reduce would have done. Constants
+// fitted to MI355X timings of every shape and split up to 8, each launch with
+// its reduce or RMSNorm and the gaps: tiles, QKV and gate/up on those 312 cases;
+// O's row and down's last price on the 8B and 70B layers and their TP2 and TP8
+// shards at 36 row counts from 66 to 2374 (one layer over and over and four in
+// turn), with the layers of hidden 5120 and 3072 left out of the fit. Loss of the
+// picks against the best measured choice, mean and worst, fitted / left out: O
+// 1.6 % and 19 % / 1.5 % and 9 % (6.5 % and 48 % / 7.6 % and 47 % while an unsplit
+// O was not charged its RMSNorm launch: 8B at M = 384 32.0 + 4.9 us on 64 x 128
+// tiles where a K split takes less than 29), down 3.0 % and 16 % / 1.4 % and 10 %
+// (3.9 % and 33 % / 1.4 % and 10 % while an unsplit down's residual and output
+// counted 33 TB/s: TP2 at M = 822 75 us unsplit, 64 with a split of 2), QKV 2.4 %,
+// gate/up 0.5 %.
 struct EpilogueCost {
-  float split_us, split_bytes_us, whole_bytes_us;  // per reduce; per MB of reduce traffic; per MB of fp32 output
+  float split_us, split_bytes_us;  // per reduce; per MB of reduce traffic
+  float whole_us, whole_bytes_us;  // per whole-K launch; per MB of fp32 output
 };
 constexpr double kHbmBytesUs = 5.589e6, kFillBytesUs = 16.197e6, kLaterRounds = 1.003, kGemmLaunchUs = 2.684;
-// QKV + RoPE, O (with the RMSNorm behind it), gate/up, down
-constexpr EpilogueCost kEpilogueCost[] = {
-    {1.32, 1 / 5.828, 0.0}, {3.477, 1 / 7.148, 1 / 2.534}, {2.474, 1 / 7.487, 0.0}, {0.0, 1 / 5.271, 1 / 16.63}};
+constexpr EpilogueCost kEpilogueCost[] = {{1.32, 1 / 5.828, 0, 0},     // QKV + RoPE
+                                          {4, 1 / 8.0, 6, 1 / 5.0},    // O, with the RMSNorm behind it
+                                          {2.474, 1 / 7.487, 0, 0},    // gate/up
+                                          {0, 1 / 5.271, 0, 1 / 5.0}};  // down
+
+static const EpilogueCost& epilogue_cost(const GemmArgs& a) {
+  return kEpilogueCost[a.epi == GEMM_QKV_ROPE ? 0 : a.epi == GEMM_SWIGLU ? 2 : a.r_f32 ? 3 : 1];
+}
 
 static double plan_cost(const GemmArgs& a, const TileCfg& c, int tiles_m, int tiles_n, int ks, int kst, int cus) {
   const int bm = 16 * c.tm * c.wr, bn = 16 * c.tn * c.wc;
@@ -1273,9 +1289,9 @@ static double plan_cost(const GemmArgs& a, const TileCfg& c, int tiles_m, int ti
   double us = kGemmLaunchUs + rounds * c.round_us;
   us += kst * (rounds == 1 ? stage(last, 1.0)
                            : stage(slots, 1.0) + (rounds - 2) * stage(slots, kLaterRounds) + stage(last, kLaterRounds));
-  const EpilogueCost& e = kEpilogueCost[a.epi == GEMM_QKV_ROPE ? 0 : a.epi == GEMM_SWIGLU ? 2 : a.r_f32 ? 3 : 1];
+  const EpilogueCost& e = epilogue_cost(a);
   const double mb = (double)a.M * partial_width(a) * 4.0e-6;
-  return us + (ks > 1 ? e.split_us + mb * (2 * ks + 1) * e.split_bytes_us : mb * e.whole_bytes_us);
+  return us + (ks > 1 ? e.split_us + mb * (2 * ks + 1) * e.split_bytes_us : e.whole_us + mb * e.whole_bytes_us);
 }
 
 // The small-batch kernel where it applies and nothing else is forced; else

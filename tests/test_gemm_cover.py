@@ -7,6 +7,7 @@ import pytest
 
 import oracle
 from gemmcover import COVER, COVER_LENS, COVER_T, CU_COUNT, MAX_KSPLIT, real_token_counts
+from hb_workloads import LLAMA3_8B, SHAPES, LayerShape
 from hbref import assert_parity, assert_stage, assert_swiglu_stage, errors, oracle_for_batch
 
 
@@ -94,3 +95,21 @@ def test_forced_grid_parity(H, monkeypatch, ksplit):
 def dl_cu():
     import torch
     return torch.cuda.get_device_properties(0).multi_processor_count
+
+
+@pytest.mark.parametrize("shape", [LLAMA3_8B, LayerShape("hidden-3072", 3072, 24, 6, 128, 8192, weight_seed=47)], ids=lambda s: s.name)
+@pytest.mark.parametrize("T", [384, 416, 448])
+def test_an_unsplit_o_projection_is_charged_its_rmsnorm_launch(H, shape, T):
+    """A K split's reduce also applies the pre-FFN RMSNorm, which is a launch of its
+    own behind an unsplit O projection. At these row counts the split wins by 15-42 %
+    (8B, 384 rows: below 29 against 37 us) and an uncharged launch hides that."""
+    cfg = H.make_config(shape, 4096, 4)
+    assert H.hb_plan_gemms(cfg, T, CU_COUNT)[H.HB_GEMM_O][1] > 1
+
+
+def test_an_unsplit_down_projection_is_charged_its_residual_and_output(H):
+    """An unsplit down projection reads the fp32 residual and writes its output in its
+    epilogue, at memory rates: TP2 shard of the 8B layer, 822 rows, 75 us unsplit
+    against 64 us with a K split of 2."""
+    cfg = H.make_config(SHAPES["llama3-8b-tp2-shard"], 4096, 4)
+    assert H.hb_plan_gemms(cfg, 822, CU_COUNT)[H.HB_GEMM_DOWN][1] > 1
