@@ -34,7 +34,10 @@ constexpr size_t kScratchBytes = (size_t)64 << 20;
 static __device__ __align__(256) uint8_t scratch[kScratchBytes];
 
 namespace {
-constexpr int kStages = 4;
+// Slots of the metadata ring: as many iterations may be enqueued before the host
+// waits for the first of them. (A slot whose copy goes over the copy stream is
+// free again after its copy, which itself waits for the slot's iteration before.)
+constexpr int kStages = 8;
 // Pinned host staging of the allocation-free entry point's metadata (int32).
 constexpr size_t kNoAllocMetaInts = (size_t)1 << 18;
 // Metadata of at most this many int32 is copied by a kernel on the layer's own

@@ -41,3 +41,34 @@ def test_uploads_in_turn_match_single_runs(hb):
     torch.cuda.synchronize()
     for n, i in enumerate(order):
         assert torch.all(torch.isfinite(got[n])) and torch.equal(got[n], want[i]), (n, i)
+
+
+@pytest.mark.parametrize("n,keys", [(2, 17), (230, 5000)], ids=["in-stream", "copy-stream"])
+def test_eight_iterations_are_enqueued_without_waiting(hb, n, keys):
+    """The call returns with its iteration enqueued: eight of them behind work that
+    the stream has not got through, none waiting for the one before."""
+    import time
+
+    import torch
+    from hb_workloads import make_weights
+    from paper_2503_22562_amd.harness import DeviceLayer
+    nb, rng = 1024, np.random.default_rng(73)
+    dl = DeviceLayer(COVER, make_weights(COVER), nb, 256, 256, pool_fill_bits=0)
+    b = _decodes(rng, nb, n, keys)
+    x = torch.zeros((n, COVER.hidden), dtype=torch.bfloat16, device="cuda")
+    y = dl.run(b, x)
+    for _ in range(20):  # every slot's buffers exist
+        dl.run(b, x, x_out=y)
+    torch.cuda._sleep(1000)
+    torch.cuda.synchronize()
+    t0 = time.perf_counter()
+    torch.cuda._sleep(1_000_000)
+    torch.cuda.synchronize()
+    per_ms = 1_000_000 / (1e3 * (time.perf_counter() - t0))
+    busy = torch.cuda.Event()
+    torch.cuda._sleep(int(per_ms * 500))
+    busy.record()
+    for i in range(8):
+        dl.run(b, x, x_out=y)
+        assert not busy.query(), i
+    torch.cuda.synchronize()
