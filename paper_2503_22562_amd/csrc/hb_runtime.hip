@@ -44,9 +44,13 @@ constexpr size_t kNoAllocMetaInts = (size_t)1 << 18;
 // stream: it costs a launch and one PCIe round trip, where the copy stream's
 // path costs two event waits and a DMA start ahead of the first kernel (one 8B
 // decode 121.8 -> 108.1 us, 32 decodes 190.6 -> 179.7, 777-token chunk + 45
-// decodes on a TP2 shard 299.0 -> 291.6). With 256 decodes (about 45 K int32)
-// the transfer has eaten the gain (596 us both ways); beyond 64 K the copy
-// stream hides it behind the previous iteration.
+// decodes on a TP2 shard 299.0 -> 291.6). The kernel's transfer is on the
+// critical path and grows with the metadata, the copy stream's hides behind the
+// previous iteration: the two are equal at about 80 K to 100 K int32. Decodes,
+// iterations in a row, in-stream against copy stream: 34 K int32 309 against 315
+// us (8B), 43 K 139 against 146 and 58 K 160 against 167 (70B TP8 shard), 67 K
+// 476 against 479, 83 K 620 against 622, 107 K 636 against 636, 137 K 787
+// against 780 (8B).
 constexpr size_t kInStreamMetaInts = (size_t)1 << 16;
 constexpr int kMaxDevices = 64;
 constexpr double kPeakHbm = 8.0e12;      // MI355X HBM3E, bytes/s
