@@ -164,16 +164,21 @@ hb_status hb_run_iteration(hb_layer* layer, const hb_batch_desc* desc);
 
 /* hb_run_iteration for callers that cannot allocate device memory during the
  * call (code under HIP graph capture, tight serving loops, harnesses that
- * forbid hipMalloc): the same kernels and launch plans (except that a GEMM's
- * K split whose partial sums do not fit the scratch gives way to the best plan
- * that does), with the iteration's scratch -- its metadata, split-K partial sums and attention split partials
- * -- in a fixed 64 MiB device array that the library holds on each GPU it
- * runs on for the life of the process (looked up when a layer is created),
- * and the metadata staged through pinned host memory the layer allocated at
- * creation (1 MiB). The call allocates no device or pinned memory and
- * records no timing events (hb_set_kernel_timing does not apply). Every call
- * on one GPU shares that GPU's array: calls whose iterations overlap on one
- * GPU (layers on different streams) race; calls on one stream are ordered.
+ * forbid hipMalloc): the same kernels and launch plans, hence the same bits,
+ * with two exceptions where the scratch is too small for them. A GEMM's K split
+ * whose partial sums do not fit gives way to the best plan that does; and a
+ * batch whose metadata or partials still do not fit has its decodes cut no
+ * finer than 1024 keys. Either adds in another fp32 order. The iteration's
+ * scratch -- its metadata, split-K partial sums and attention split partials --
+ * is a fixed 64 MiB device array that the library holds on each GPU it runs on
+ * for the life of the process (looked up when a layer is created). The metadata
+ * is staged through pinned host memory the layer allocated at creation (1 MiB);
+ * under graph capture it travels inside the graph, so a replay computes the
+ * captured batch whatever the layer ran since. The call allocates no device or
+ * pinned memory and records no timing events (hb_set_kernel_timing does not
+ * apply). Every call on one GPU shares that GPU's array: calls whose iterations
+ * overlap on one GPU (layers on different streams) race; calls on one stream
+ * are ordered.
  * Errors: those of hb_run_iteration, and HB_ERR_UNSUPPORTED for a batch whose
  * scratch exceeds 64 MiB or whose metadata exceeds 2^18 int32 (nothing is
  * enqueued then). */

@@ -140,3 +140,4 @@ def test_noalloc_cuts_items_coarser_when_metadata_does_not_fit(hb):
     got, want = y_na.cpu().numpy(), y.cpu().numpy()
     assert np.array_equal(got[:94000], want[:94000])  # chunks: the same work units
     assert_parity(got[94000:], want[94000:])          # decodes: the same keys over other splits
+    assert not np.array_equal(got[94000:], want[94000:]), "the decodes were not cut coarser"
