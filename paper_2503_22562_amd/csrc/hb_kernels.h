@@ -46,7 +46,7 @@ struct RopePrep {
 void launch_rmsnorm(hipStream_t s, const void* x, bool x_f32, const uint16_t* g, uint16_t* out, int T, int H,
                     float eps, const RopePrep* rope = nullptr);
 
-enum GemmEpilogue { GEMM_STORE_BF16 = 0, GEMM_RESIDUAL = 1, GEMM_SWIGLU = 2, GEMM_QKV_ROPE = 3 };
+enum GemmEpilogue { GEMM_RESIDUAL = 1, GEMM_SWIGLU = 2, GEMM_QKV_ROPE = 3 };
 
 // Rows past M that a GEMM's A operand must keep readable (kGemmPadRows, in
 // hb_plan.h): the LDS-pipelined kernels load whole row tiles (at most 288
@@ -54,8 +54,7 @@ enum GemmEpilogue { GEMM_STORE_BF16 = 0, GEMM_RESIDUAL = 1, GEMM_SWIGLU = 2, GEM
 // (8-row load groups). Every operand must fit kOperandWindow bytes.
 
 // C[M][N] = A[M][K] * B[N][K]^T with an epilogue:
-//   GEMM_STORE_BF16: C bf16
-//   GEMM_RESIDUAL:   C = R + A B^T, R bf16 or fp32, C fp32 or bf16
+//   GEMM_RESIDUAL:   C = R + A B^T, R bf16, fp32 or null, C fp32 or bf16
 //   GEMM_SWIGLU:     B has 2N rows [gate | up]; C bf16 = silu(A Bg^T) * (A Bu^T)
 //   GEMM_QKV_ROPE:   the columns are [q heads | k heads | v heads] of head_dim
 //                    each; q and k are rotated (rotate-half RoPE with the

@@ -154,7 +154,6 @@ static void launch_gemm_regstaged(hipStream_t s, const GemmArgs& a) {
   const int ncols = (a.epi == GEMM_SWIGLU) ? 64 : BN;
   dim3 grid((a.N + ncols - 1) / ncols, (a.M + BM - 1) / BM);
   switch (a.epi) {
-    case GEMM_STORE_BF16: gemm_kernel<GEMM_STORE_BF16><<<grid, 256, 0, s>>>(a); break;
     case GEMM_RESIDUAL: gemm_kernel<GEMM_RESIDUAL><<<grid, 256, 0, s>>>(a); break;
     default: gemm_kernel<GEMM_SWIGLU><<<grid, 256, 0, s>>>(a); break;
   }
@@ -707,9 +706,7 @@ __global__ __launch_bounds__(64 * WR * WC) void gemm_pipe_kernel(GemmArgs a, int
   } else if (EPI != GEMM_SWIGLU) {
     const int nw = nt * BN + wn * WN;
     const uint32_t ld = a.ldc;
-    if (EPI == GEMM_STORE_BF16) {
-      epi_rows<TM, TN, 0, false>(a, strip, acc, a.C, ld, mw, nw, lane);
-    } else if (!a.R) {
+    if (!a.R) {
       if (a.c_f32) epi_rows<TM, TN, 0, true>(a, strip, acc, a.C, ld, mw, nw, lane);
       else epi_rows<TM, TN, 0, false>(a, strip, acc, a.C, ld, mw, nw, lane);
     } else if (a.r_f32) {
@@ -1350,7 +1347,6 @@ GemmPlan plan_gemm(const GemmArgs& a, int cu_count, int force_cfg, int force_ksp
   return p;
 }
 
-
 bool launch_gemm(hipStream_t s, const GemmArgs& a, const GemmPlan& p, float* partial) {
   if (a.M <= 0 || a.N <= 0) return false;
   if (p.cfg < 0) {
@@ -1359,7 +1355,6 @@ bool launch_gemm(hipStream_t s, const GemmArgs& a, const GemmPlan& p, float* par
   }
   if (p.cfg == kStreamTile) {
     switch (a.epi) {
-      case GEMM_STORE_BF16: launch_stream<GEMM_STORE_BF16>(s, a, p.tiles_n); break;
       case GEMM_QKV_ROPE: launch_stream<GEMM_QKV_ROPE>(s, a, p.tiles_n); break;
       case GEMM_RESIDUAL: launch_stream<GEMM_RESIDUAL>(s, a, p.tiles_n); break;
       default: launch_stream<GEMM_SWIGLU>(s, a, p.tiles_n); break;
@@ -1367,7 +1362,6 @@ bool launch_gemm(hipStream_t s, const GemmArgs& a, const GemmPlan& p, float* par
     return false;
   }
   switch (a.epi) {
-    case GEMM_STORE_BF16: launch_cfg<GEMM_STORE_BF16>(p.cfg, s, a, p.tiles_m, p.tiles_n, p.ksplit, p.kchunk, partial); break;
     case GEMM_QKV_ROPE: launch_cfg<GEMM_QKV_ROPE>(p.cfg, s, a, p.tiles_m, p.tiles_n, p.ksplit, p.kchunk, partial); break;
     case GEMM_RESIDUAL: launch_cfg<GEMM_RESIDUAL>(p.cfg, s, a, p.tiles_m, p.tiles_n, p.ksplit, p.kchunk, partial); break;
     default: launch_cfg<GEMM_SWIGLU>(p.cfg, s, a, p.tiles_m, p.tiles_n, p.ksplit, p.kchunk, partial); break;
@@ -1384,8 +1378,7 @@ bool launch_gemm(hipStream_t s, const GemmArgs& a, const GemmPlan& p, float* par
     switch (a.epi) {
       case GEMM_QKV_ROPE: launch_reduce<GEMM_QKV_ROPE>(s, a, p.ksplit, partial); break;
       case GEMM_SWIGLU: launch_reduce<GEMM_SWIGLU>(s, a, p.ksplit, partial); break;
-      case GEMM_RESIDUAL: launch_reduce<GEMM_RESIDUAL>(s, a, p.ksplit, partial); break;
-      default: launch_reduce<GEMM_STORE_BF16>(s, a, p.ksplit, partial); break;
+      default: launch_reduce<GEMM_RESIDUAL>(s, a, p.ksplit, partial); break;
     }
   }
   return false;
