@@ -1139,6 +1139,15 @@ void launch_cfg(int idx, hipStream_t s, const GemmArgs& a, int tm, int tn, int k
 // without a K split: a 128256-row head at M = 24 204 us here against 191 us
 // (at M = 1 160 against 193 us, at M = 16 194 against 193 us).
 //
+// Forced, the best tile and split would win on this side of the lines too: O, whose
+// split does the RMSNorm that here is a launch of its own, at M = 17-64 (8B 19-22
+// us here, 17-18 on 64 x 128 tiles with splits of 6 to 8; 70B 44-49, 38-42), 8B down
+// at M = 40-64 (40-43, 31-33), a 28K x 5K gate/up at M = 17-32 (59-64, 54), a 96000
+// x 8192 head at M = 17-32 (418-433; on tiles 380 at M = 40). The cost model does
+// not find those splits: it takes 70B QKV at M = 64 with a split of 2, 50 us, where
+// 3 takes 41. Nor is this kernel ahead of the two-stage 64 x 256 tiles it replaced
+// everywhere: 70B QKV at M = 17-32 47-49 us, 41-42 with those, O 44-45, 40-41.
+//
 // RT: the least bytes through the fullest CU, ceil(units / CUs) workgroups of
 // 2 RT KB of weights and g KB of activations per step. 8B down at M = 32: RT
 // 1 (256 workgroups) 34.1 us, RT 2 (128) 41.1 us; gate/up at M = 48: RT 2
